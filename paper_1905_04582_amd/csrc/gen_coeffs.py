@@ -14,6 +14,11 @@ Everything is computed here from the mathematics with mpmath (50 digits):
   product exp(-z^2) erfcx(z) is 0 whatever erfcx is.  A second, shorter FP64
   rational covers [2.1, 6.6] only (t = z sqrt 2 from 2.97 to 9.33), for the
   wavefronts whose pairs all lie at t >= 3.
+* The FP64 sweep's near pairs need q = 1 - Phi(t) = e R(t), e = exp(-t^2/2)
+  and R(t) = erfcx(t/sqrt 2)/2, to an absolute error only (q enters as 1 - q),
+  so R is fitted as P(t)/Q(t), Q(0) = 1, with weight e on [0, 9] (9 the sweep's
+  skip point): a far shorter rational than a relative fit.  Its exponential is 2^f on |f| <= 1/2, a polynomial with
+  constant term 1 (Chebyshev interpolation of (2^f - 1)/f).
 * exp(r) on |r| <= ln(2)/2 by its Taylor polynomial (FP64), after the
   Cody-Waite reduction x = k ln 2 + r with ln 2 split into a head with 20
   trailing zero bits and a tail.
@@ -76,6 +81,53 @@ def fit_erfcx(n: int, zmax, npts: int = 500, iters: int = 12, zmin=0):
         sw = sum(w)
         w = [wi / sw * npts for wi in w]
     return best[1], best[2]
+
+
+def near_ratio(t):
+    return erfcx(t / mp.sqrt(2)) / 2
+
+
+def fit_near(m: int, n: int, tmax, npts: int = 240, iters: int = 22):
+    """R(t) ~ P(t)/Q(t), deg P = m, deg Q = n, Q(0) = 1, on [0, tmax] with
+    weight exp(-t^2/2), by the same iteration as fit_erfcx."""
+    ts = [tmax * (1 - mp.cos(mp.pi * (k + mp.mpf(1) / 2) / npts)) / 2 for k in range(npts)]
+    ys = [near_ratio(t) for t in ts]
+    wt = [mp.exp(-t * t / 2) for t in ts]
+    w, qprev, best = [mp.mpf(1)] * npts, [mp.mpf(1)] * npts, None
+    for _ in range(iters):
+        A, b = mp.matrix(npts, m + 1 + n), mp.matrix(npts, 1)
+        for i, (t, y) in enumerate(zip(ts, ys)):
+            s = w[i] * wt[i] / qprev[i]
+            for k in range(m + 1):
+                A[i, k] = s * t ** k
+            for k in range(n):
+                A[i, m + 1 + k] = -s * y * t ** (k + 1)
+            b[i] = s * y
+        sol = mp.qr_solve(A, b)[0]
+        p = [sol[k] for k in range(m + 1)]
+        q = [mp.mpf(1)] + [sol[m + 1 + k] for k in range(n)]
+        qprev = [mp.polyval(q[::-1], t) for t in ts]
+        errs = [abs((mp.polyval(p[::-1], t) / v - y) * e)
+                for t, v, y, e in zip(ts, qprev, ys, wt)]
+        worst = max(errs)
+        if best is None or worst < best[0]:
+            best = (worst, p, q)
+        w = [wi * mp.sqrt(e / worst) for wi, e in zip(w, errs)]
+        top = max(w)
+        w = [wi / top + mp.mpf(10) ** -12 for wi in w]
+    return best[1], best[2]
+
+
+def check_near(p, q, tmax, dt):
+    ts = np.linspace(0.0, float(tmax), 4001).astype(dt)
+    r = (horner_np([float(v) for v in p], ts, dt).astype(np.longdouble) /
+         horner_np([float(v) for v in q], ts, dt).astype(np.longdouble))
+    ref = np.array([float(near_ratio(mp.mpf(float(t)))) for t in ts], dtype=np.longdouble)
+    return float(np.max(np.abs(r - ref) * np.exp(-ts.astype(np.longdouble) ** 2 / 2)))
+
+
+def exp2_slope(f):
+    return mp.log(2) if abs(f) < mp.mpf(10) ** -30 else mp.expm1(f * mp.log(2)) / f
 
 
 def horner_np(c, x, dt):
@@ -176,6 +228,19 @@ def main():
     lines.append(f"constexpr double kErfcxFarZmax64 = {float(zf1)!r};")
     lines.append(emit_array("kErfcxFarP64", pf, np.float64))
     lines.append(emit_array("kErfcxFarQ64", qf, np.float64))
+
+    # the sweep's near pairs
+    tnear = mp.mpf(9)
+    pn, qn = fit_near(6, 7, tnear)
+    en = check_near(pn, qn, tnear, np.float64)
+    lines.append(f"// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, {tnear}] (FP64); worst absolute error "
+                 f"of exp(-t^2/2) P/Q {en:.2e} with FP64 arithmetic")
+    lines.append(emit_array("kNearP64", pn, np.float64))
+    lines.append(emit_array("kNearQ64", qn, np.float64))
+    e2 = [mp.mpf(1)] + cheb_fit(exp2_slope, -mp.mpf(1) / 2, mp.mpf(1) / 2, 10)
+    e2_err = check_poly(e2, lambda f: mp.mpf(2) ** f, -mp.mpf(1) / 2, mp.mpf(1) / 2, np.float64)
+    lines.append(f"// 2^f on |f| <= 1/2, degree 11; worst relative error {e2_err:.2e}")
+    lines.append(emit_array("kExp2C64", e2, np.float64))
 
     # ---- exp: Cody-Waite split of ln 2 and Taylor coefficients
     ln2 = mp.log(2)

@@ -73,6 +73,41 @@ constexpr double kErfcxFarQ64[8] = {
     0x1.bc87206f17fe2p-4,
     0x1.893e076c0501fp-7};
 
+// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, 9.0] (FP64); worst absolute error of exp(-t^2/2) P/Q 1.09e-16 with FP64 arithmetic
+constexpr double kNearP64[7] = {
+    0x1.0000000000000p-1,
+    0x1.0123d7ff1a05cp-1,
+    0x1.048a255fe3197p-2,
+    0x1.3b4dc0833b57dp-4,
+    0x1.da0a7807e229cp-7,
+    0x1.a0a7478e177a7p-10,
+    0x1.4f95c0a2fc844p-14};
+
+constexpr double kNearQ64[8] = {
+    0x1.0000000000000p+0,
+    0x1.cd66019dbbbb2p+0,
+    0x1.72699b494c041p+0,
+    0x1.58b150a3fc54ep-1,
+    0x1.936b2b80d61d0p-3,
+    0x1.2aadb60993e59p-5,
+    0x1.051bdcd2e141fp-8,
+    0x1.a495ec5711708p-13};
+
+// 2^f on |f| <= 1/2, degree 11; worst relative error 2.12e-16
+constexpr double kExp2C64[12] = {
+    0x1.0000000000000p+0,
+    0x1.62e42fefa39efp-1,
+    0x1.ebfbdff82c598p-3,
+    0x1.c6b08d704a0c2p-5,
+    0x1.3b2ab6fba1ddap-7,
+    0x1.5d87fe78a5276p-10,
+    0x1.430913096fd9fp-13,
+    0x1.ffcbfc670dcd4p-17,
+    0x1.62bfd47773353p-20,
+    0x1.b524fae627834p-24,
+    0x1.e6063f7217bc6p-28,
+    0x1.e9d3fe3952179p-32};
+
 // exp(x) = 2^k exp(r), x = k ln2 + r, |r| <= ln2/2; ln2 = head + tail with
 // head on 33 significant bits so that k*head is exact for |k| < 2^20
 constexpr double kLn2Head = 0x1.62e42fef00000p-1;

@@ -62,6 +62,9 @@ struct CoefTables64 {
     double erfcx_fp[sizeof(kErfcxFarP64) / sizeof(double)];
     double erfcx_fq[sizeof(kErfcxFarQ64) / sizeof(double)];
     double log1p[kLog1pN];  // 1/(k+1), k = 0 .. kLog1pN-1
+    double near_p[sizeof(kNearP64) / sizeof(double)];
+    double near_q[sizeof(kNearQ64) / sizeof(double)];
+    double exp2[sizeof(kExp2C64) / sizeof(double)];
 };
 
 constexpr CoefTables64 make_tables64()
@@ -76,6 +79,9 @@ constexpr CoefTables64 make_tables64()
     for (size_t k = 0; k < sizeof(kErfcxFarQ64) / sizeof(double); ++k)
         t.erfcx_fq[k] = kErfcxFarQ64[k];
     for (int k = 0; k < kLog1pN; ++k) t.log1p[k] = 1.0 / (k + 1);
+    for (size_t k = 0; k < sizeof(kNearP64) / sizeof(double); ++k) t.near_p[k] = kNearP64[k];
+    for (size_t k = 0; k < sizeof(kNearQ64) / sizeof(double); ++k) t.near_q[k] = kNearQ64[k];
+    for (size_t k = 0; k < sizeof(kExp2C64) / sizeof(double); ++k) t.exp2[k] = kExp2C64[k];
     return t;
 }
 
@@ -257,6 +263,93 @@ __device__ __forceinline__ void trunc_terms2_far_f64(double t1, double t2, doubl
     mills2 = kInvSqrt2Pi * e2 * g2;
 }
 
+// The sweep's truncation terms.  Its sums need sum ln Phi(t) and m =
+// phi(t)/Phi(t) of each near pair (t below the sweep's skip point), and the
+// first only as a sum: it is -ln of the product of the pairs' 1/Phi, so a pair
+// costs one multiplication instead of a logarithm.  With e = exp(-t^2/2) and
+// 1 - Phi = e P/Q (fitted to an absolute error of 2^-53),
+//     1/Phi = Q / (Q - e P),   sigma m = (sigma/sqrt(2 pi)) e (1/Phi),
+// from one reciprocal.  Against the relative forms above (trunc_terms2_f64
+// and its far-range variant: 84 and 71 instructions a pair) this is 45, in
+// one form for every near t, with 26 coefficients instead of 44.
+
+// what the near terms take from sigma, formed once per wave
+struct NearConst64 {
+    double inv_s;  // 1/sigma
+    double c2;     // -log2(e) / (2 sigma^2): log2 of exp(-t^2/2) over delta^2
+    double kappa;  // sigma / sqrt(2 pi)
+};
+__device__ __forceinline__ NearConst64 near_const(double sigma, double inv_s)
+{
+    return {inv_s, -0.5 * kLog2e * inv_s * inv_s, sigma * kInvSqrt2Pi};
+}
+
+constexpr int kNearPN = sizeof(kNearP64) / sizeof(double);
+constexpr int kNearQN = sizeof(kNearQ64) / sizeof(double);
+constexpr int kExp2N = sizeof(kExp2C64) / sizeof(double);
+
+// exp(-t^2/2) of a near pair from s2 = delta^2: 2^y, y = c2 s2 = k + f, with k
+// read from the low word of y + 1.5 2^52 and added to the exponent field.  For
+// a pair that is not near the result is meaningless (the caller drops it).
+__device__ __forceinline__ double near_scale(double p, double shifted)
+{
+    const int k = __double2loint(shifted);
+    return __hiloint2double(__double2hiint(p) + (int)((unsigned)k << 20), __double2loint(p));
+}
+
+// Two pairs, sharing every coefficient load: s2 = delta^2, dl = delta; `na`,
+// `nb`: whether the pair is near (one that is not gets g = 1 to rounding and
+// m = 0).  g = 1/Phi(t), m = sigma phi(t)/Phi(t).
+__device__ __forceinline__ void near_terms2_f64(double s2a, double s2b, double dla, double dlb,
+                                                bool na, bool nb, const NearConst64& k,
+                                                tab64_ptr tb, double& ga, double& gb, double& ma,
+                                                double& mb)
+{
+    constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
+    const double ha = fma(s2a, k.c2, kMagic), hb = fma(s2b, k.c2, kMagic);
+    const double fa = fma(s2a, k.c2, -(ha - kMagic)), fb = fma(s2b, k.c2, -(hb - kMagic));
+    double pa, pb;
+    horner2_tab<kExp2N - 1>(tb->exp2 + 1, fa, fb, pa, pb);
+    pa = fma(pa, fa, 1.0);
+    pb = fma(pb, fb, 1.0);
+    const double ea = na ? near_scale(pa, ha) : 0.0;
+    const double eb = nb ? near_scale(pb, hb) : 0.0;
+    // (the bound keeps P and Q finite for pairs that are not near)
+    const double ta = fmin(dla * k.inv_s, 10.0), tb2 = fmin(dlb * k.inv_s, 10.0);
+    double Pa, Pb, Qa, Qb;
+    horner2_tab<kNearPN>(tb->near_p, ta, tb2, Pa, Pb);
+    horner2_tab<kNearQN - 1>(tb->near_q + 1, ta, tb2, Qa, Qb);
+    Qa = fma(Qa, ta, 1.0);
+    Qb = fma(Qb, tb2, 1.0);
+    const double da = fma(-ea, Pa, Qa), db = fma(-eb, Pb, Qb);
+    // Q/d: the hardware reciprocal r (relative error v below 2^-22), then the
+    // quotient by 1 + v + v^2
+    const double ra = __builtin_amdgcn_rcp(da), rb = __builtin_amdgcn_rcp(db);
+    const double va = fma(-da, ra, 1.0), vb = fma(-db, rb, 1.0);
+    const double qa = Qa * ra, qb = Qb * rb;
+    ga = fma(qa, fma(va, va, va), qa);
+    gb = fma(qb, fma(vb, vb, vb), qb);
+    ma = (ea * k.kappa) * ga;
+    mb = (eb * k.kappa) * gb;
+}
+
+// ln g for a product g of up to 256 factors 1/Phi in [1, 2] (to rounding):
+// g = 2^n h, h in [1/2, 1), ln h = ln c + 2 atanh((h - c)/(h + c)) about
+// c = sqrt(1/2), |(h - c)/(h + c)| < 0.172
+__device__ __forceinline__ double log_product(double g, tab64_ptr tb)
+{
+    constexpr double kLn2 = 0.693147180559945309417;
+    const int n = __builtin_amdgcn_frexp_exp(g);
+    const double h = __builtin_amdgcn_frexp_mant(g);
+    const double d = h + kInvSqrt2;
+    const double r = __builtin_amdgcn_rcp(d);
+    const double v = fma(-d, r, 1.0);
+    const double q = (h - kInvSqrt2) * r;
+    const double s = fma(q, fma(v, v, v), q);
+    const double a = horner_tab<kAtanhN>(tb->atanh, s * s);
+    return fma(2.0 * s, a, ((double)n - 0.5) * kLn2);
+}
+
 // ---------------------------------------------------------------- FP32 --
 
 // ln Phi(t) and phi(t)/Phi(t) for t >= 0 in FP32 arithmetic
@@ -272,6 +365,25 @@ __device__ __forceinline__ void trunc_terms_f32(float t, float& lnphi, float& mi
     const float rr = __builtin_amdgcn_rcpf(d1 * d2);
     const float s = a * d2 * rr;
     lnphi = -2.0f * s * horner(kAtanhA32, s * s);
+    mills = (float)(4.0 * kInvSqrt2Pi) * (e * Q) * (d1 * rr);
+}
+
+// The sweep's form of trunc_terms_f32, same roundings: h = -ln Phi(t)/2 (the
+// factor -2 is exact and taken out of the sum), and a pair with ok = false
+// gets h = m = 0 from e = 0 (z is bounded, so P and Q are finite).
+__device__ __forceinline__ void near_terms_f32(float t, bool ok, float& h, float& mills)
+{
+    const float x = __builtin_amdgcn_exp2f((t * t) * (float)(-0.5 * kLog2e));
+    const float e = ok ? x : 0.0f;
+    const float z = fminf(t * (float)kInvSqrt2, kErfcxZmax32 + 1.0f);
+    const float P = horner(kErfcxP32, z);
+    const float Q = horner(kErfcxQ32, z);
+    const float a = e * P;
+    const float d1 = fmaf(4.0f, Q, -a);
+    const float d2 = d1 - a;
+    const float rr = __builtin_amdgcn_rcpf(d1 * d2);
+    const float s = a * d2 * rr;
+    h = s * horner(kAtanhA32, s * s);
     mills = (float)(4.0 * kInvSqrt2Pi) * (e * Q) * (d1 * rr);
 }
 

@@ -20,10 +20,13 @@
 //     and the pair then adds one product to the wave's sums: the residual
 //     square, which both the likelihood and dL/dsigma scale by a power of
 //     1/sigma once per wave, and its gradient coefficient (scaled by
-//     1/sigma^2 once per staging batch in FP32, once per walk in FP64); in
-//     FP64 a wavefront whose pairs in
-//     two rows all have delta/sigma >= 3 takes shorter far-range forms of the
-//     special functions;
+//     1/sigma^2 once per staging batch in FP32, once per walk in FP64);
+//   * in FP64 a near pair costs 45 vector instructions more (near_terms2_f64);
+//     the sweep is bound by vector issue (86% busy at N = 20000, the clock
+//     held near 1.8 GHz by the FP64 load), so they are most of its time where
+//     few wavefronts skip.  N = 20000, D = 2, sigma = 0.5: 579 -> 484 us per
+//     evaluation with them; N = 5392, sigma = 0.3: 50.2 -> 45.4 us.  FP32 keeps
+//     its relative forms: their roundings set the result's last digits;
 //   * the column sums of the wr waves of a column group, and the row sums of
 //     the wc waves of a row group, meet in LDS and are added in wave order;
 //     column, row and scalar partials of the tile go to the workspace, and
@@ -72,21 +75,6 @@ template <>
 __device__ __forceinline__ float rsqrt_t<float>(float x)
 {
     return __builtin_amdgcn_rsqf(x);
-}
-
-// both rows of a two-row step (`tb`: the FP64 coefficient tables)
-template <typename T>
-__device__ __forceinline__ void trunc_terms2(T t1, T t2, T& l1, T& m1, T& l2, T& m2, tab64_ptr)
-{
-    trunc_terms_f32(t1, l1, m1);
-    trunc_terms_f32(t2, l2, m2);
-}
-template <>
-__device__ __forceinline__ void trunc_terms2<double>(double t1, double t2, double& l1,
-                                                     double& m1, double& l2, double& m2,
-                                                     tab64_ptr tb)
-{
-    trunc_terms2_f64(t1, t2, l1, m1, l2, m2, tb);
 }
 
 // Skip point of the truncation terms.  For t >= T, 0 <= -ln Phi(t) <=
@@ -171,11 +159,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
     double gj[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) gj[d] = 0.0;
-    // the wave's sums over its pairs: A = sum (y - delta)^2, Lsum = sum ln Phi(t),
-    // Msum = sum delta phi(t)/Phi(t); the tile's r and dsigma sums follow from
-    // them (r = A / (2 sigma^2) + Lsum, dsigma terms = A / sigma^3 + Msum /
-    // sigma^2), so a pair past the skip point adds one product to them
-    double acc_A = 0.0, acc_L = 0.0, acc_M = 0.0;
+    // the wave's sums over its pairs: A = sum (y - delta)^2, L = sum ln Phi(t)
+    // and M = sum delta phi(t)/Phi(t) (FP64: times sigma); the tile's r and
+    // dsigma sums follow from them (r = A / (2 sigma^2) + L, dsigma terms = A /
+    // sigma^3 + M / sigma^2), so a pair past the skip point adds one product to
+    // them.  FP64 carries L as G, the product of the near pairs' 1/Phi (at most
+    // 2^256 over a walk's 256 rows); FP32 sums -ln Phi / 2.
+    double acc_A = 0.0, acc_G = 1.0, acc_M = 0.0, acc_L = 0.0;
     int cnt = 0;
     // sigma is read-only for the launch: a scalar load
     const double sig = *(const_f64_ptr)a.sigma;
@@ -187,19 +177,17 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
 #pragma unroll
         for (int d = 0; d < D; ++d) xj[d] = colok ? a.x[j * a.ldx + d] : 0.0;
         const T sigT = (T)sig, inv_sT = (T)inv_s;
+        const NearConst64 nc = near_const(sig, inv_s);  // (FP64)
+        int near_steps = 0;  // whether any step took the truncation terms (FP64)
         // skip test on the squared distance: s2 >= (skip point * sigma)^2
         // means t >= the skip point (to the rounding of the bound).  The
         // model without truncation has no ln Phi and m terms: a negative
         // bound sends every step past them.
         const double tb = (double)skip_t<T>() * sig;
         const T thr2 = a.truncated ? (T)(tb * tb) : T(-1);
-        // FP64: a step whose pairs all lie at t >= kFarT takes the shorter
-        // far-range forms of the special functions
-        const double tf = kFarT * sig;
-        const T thrf = (T)(tf * tf);
         const T* __restrict__ Y = static_cast<const T*>(a.y);
-        // the FP64 special functions' coefficient tables, addressed once
-        const tab64_ptr ctab = sizeof(T) == 8 ? tab64() : nullptr;
+        // the FP64 coefficient tables, addressed once
+        const tab64_ptr ctab = tab64();
 
         // Y is read two steps (four rows) ahead of use into two register
         // pairs that alternate, so each load has two steps of arithmetic to
@@ -248,22 +236,25 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
         const int o = lane / RG, h = lane % RG;
         const int orow = o / D, odim = o % D;
 
+        constexpr bool BATCH_SUMS = sizeof(T) < sizeof(double);
         T gjb[D];
-        T bA, bL, bM;
+        T bA, bG, bM;
         auto batch_reset = [&]() {
 #pragma unroll
             for (int d = 0; d < D; ++d) gjb[d] = T(0);
             bA = T(0);
-            bL = T(0);
+            bG = BATCH_SUMS ? T(0) : T(1);
             bM = T(0);
         };
-        // In FP32 the lane sums (bA, bL, bM, gjb) close into the FP64
+        // In FP32 the lane sums (bA, bG, bM, gjb) close into the FP64
         // accumulators at the end of each staging batch; in FP64 they are
         // those accumulators and run over the whole walk.
-        constexpr bool BATCH_SUMS = sizeof(T) < sizeof(double);
         auto close_sums = [&]() {
             acc_A += (double)bA;
-            acc_L += (double)bL;
+            if constexpr (BATCH_SUMS)
+                acc_L += -2.0 * (double)bG;
+            else
+                acc_G = bG;
             acc_M += (double)bM;
 #pragma unroll
             for (int d = 0; d < D; ++d) gj[d] = fma((double)gjb[d], inv_s2, gj[d]);
@@ -331,10 +322,10 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
             cnt += (int)__builtin_popcountll(ma) + (int)__builtin_popcountll(mb);
             const bool oka = __builtin_amdgcn_inverse_ballot_w64(ma);
             const bool okb = __builtin_amdgcn_inverse_ballot_w64(mb);
-            // any observed pair closer than the skip point sends the wave
-            // through the special functions (the others' terms are masked)
-            const uint64_t near = (__builtin_amdgcn_ballot_w64(s2a < thr2) & ma) |
-                                  (__builtin_amdgcn_ballot_w64(s2b < thr2) & mb);
+            // near: the observed pairs closer than the skip point; any sends
+            // the wave through the truncation terms
+            const uint64_t na = __builtin_amdgcn_ballot_w64(s2a < thr2) & ma;
+            const uint64_t nb = __builtin_amdgcn_ballot_w64(s2b < thr2) & mb;
             // delta and 1/delta from one reciprocal square root of s2 clamped
             // to the smallest normal number.  A coincident pair (s2 = 0) gets
             // delta = 0 and a gradient term (coefficient) * (x_i - x_j) = 0;
@@ -342,37 +333,46 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
             // term stays below the residual in size, as it is at any distance
             const T rsa = rsqrt_t(fmax(s2a, min_normal<T>()));
             const T rsb = rsqrt_t(fmax(s2b, min_normal<T>()));
-            // a pair outside the sums gets residual 0 (and, below, ln Phi =
-            // m = 0): all its terms vanish
-            const T ra = oka ? fma(-s2a, rsa, ya) : T(0);
-            const T rb = okb ? fma(-s2b, rsb, yb) : T(0);
+            // residuals delta - y; a pair outside the sums gets 0 (and is not
+            // near): all its terms vanish
+            const T ra = oka ? fma(s2a, rsa, -ya) : T(0);
+            const T rb = okb ? fma(s2b, rsb, -yb) : T(0);
             bA = fma(ra, ra, bA);
             bA = fma(rb, rb, bA);
-            // sigma^2 w (x_i - x_j)/delta = (m sigma - (y - delta)) (x_i -
-            // x_j)/delta; far pairs (t past the skip point for every lane of
-            // the wave) take m = ln Phi = 0 without evaluating them
-            T ca = -ra * rsa, cb = -rb * rsb;
-            if (near) {
-                const T dla = s2a * rsa, dlb = s2b * rsb;
-                T la, mla, lb, mlb;
-                if constexpr (sizeof(T) == 8) {
-                    if ((__builtin_amdgcn_ballot_w64(s2a < thrf) |
-                         __builtin_amdgcn_ballot_w64(s2b < thrf)) == 0)
-                        trunc_terms2_far_f64(dla * inv_sT, dlb * inv_sT, la, mla, lb, mlb, ctab);
-                    else
-                        trunc_terms2<T>(dla * inv_sT, dlb * inv_sT, la, mla, lb, mlb, ctab);
-                } else {
-                    trunc_terms2<T>(dla * inv_sT, dlb * inv_sT, la, mla, lb, mlb, ctab);
+            // sigma^2 w (x_i - x_j)/delta = (delta - y + m sigma) (x_i -
+            // x_j)/delta, m = 0 past the skip point
+            T ca, cb;
+            if constexpr (sizeof(T) == 8) {
+                T wa = ra, wb = rb;
+                if (na | nb) {
+                    const T dla = s2a * rsa, dlb = s2b * rsb;
+                    T ga, gb, mla, mlb;
+                    near_terms2_f64(s2a, s2b, dla, dlb, __builtin_amdgcn_inverse_ballot_w64(na),
+                                    __builtin_amdgcn_inverse_ballot_w64(nb), nc, ctab, ga, gb,
+                                    mla, mlb);
+                    near_steps = 1;
+                    bG *= ga * gb;
+                    bM = fma(dla, mla, bM);
+                    bM = fma(dlb, mlb, bM);
+                    wa += mla;
+                    wb += mlb;
                 }
-                la = oka ? la : T(0);
-                mla = oka ? mla : T(0);
-                lb = okb ? lb : T(0);
-                mlb = okb ? mlb : T(0);
-                bL += la + lb;
-                bM = fma(dla, mla, bM);
-                bM = fma(dlb, mlb, bM);
-                ca = fma(mla * sigT, rsa, ca);
-                cb = fma(mlb * sigT, rsb, cb);
+                ca = wa * rsa;
+                cb = wb * rsb;
+            } else {
+                ca = ra * rsa;
+                cb = rb * rsb;
+                if (na | nb) {
+                    const T dla = s2a * rsa, dlb = s2b * rsb;
+                    T ha, hb, mla, mlb;
+                    near_terms_f32(dla * inv_sT, oka, ha, mla);
+                    near_terms_f32(dlb * inv_sT, okb, hb, mlb);
+                    bG += ha + hb;
+                    bM = fma(dla, mla, bM);
+                    bM = fma(dlb, mlb, bM);
+                    ca = fma(mla * sigT, rsa, ca);
+                    cb = fma(mlb * sigT, rsb, cb);
+                }
             }
             if (GRAD) {
                 T* st = stage + (size_t)q * SROW + (size_t)lane * D;
@@ -456,10 +456,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
             if (q != 0) batch_flush(general_walk, ib - q);
         }
         if constexpr (!BATCH_SUMS) close_sums();
+        if (near_steps) acc_L = -log_product(acc_G, ctab);
     }
 
     double acc_r = fma(acc_A, 0.5 * inv_s2, acc_L);
-    double acc_s = fma(acc_A, inv_s2 * inv_s, acc_M * inv_s2);
+    double acc_s = sizeof(T) == 8 ? (acc_A + acc_M) * (inv_s2 * inv_s)
+                                  : fma(acc_A, inv_s2 * inv_s, acc_M * inv_s2);
 
     const int wr = a.wr;
     double* cp = a.colpart + (((size_t)c * a.nrb + r) * cw + (size_t)wu * kWave + lane) * D;
