@@ -9,9 +9,15 @@
 // here is the Hilbert curve for D = 2 and bit interleaving (Morton order) for
 // other D, on coordinates quantised over the bounding box of X.
 //
-// Everything runs in one work-group: a bounding-box pass, a key pass and a
-// stable least-significant-digit radix sort (4-bit digits, 8 passes).  The
-// cost is a few passes over N keys, once per problem.
+// Up to kRankMaxN locations the stable sort is a count: the position of a
+// location is the number of locations with a smaller key, or the same key and
+// a smaller index.  N^2 comparisons of two instructions each spread over the
+// whole chip, where a radix sort's passes follow one another: at N = 5392 the
+// bounding box, keys and ranks take 21 us against 96 us for the radix sort
+// below.  It runs in one work-group (a bounding-box pass, a key pass and a
+// stable least-significant-digit sort, 4-bit digits, 8 passes), and its time
+// grows as N (17 us per thousand), the count's as N^2 (80 us at N = 32768):
+// they meet near N = 2 * 10^5.
 #include "../../include/massivemds.h"
 #include "mds_internal.h"
 
@@ -74,6 +80,114 @@ __device__ uint32_t point_key(const double* xi, int d, const double* lo, const d
         for (int dd = 0; dd < d; ++dd) key |= ((q[dd] >> k) & 1u) << (k * d + dd);
     return key;
 }
+
+// ---- by ranks
+
+constexpr int64_t kRankMaxN = 131072;
+constexpr int kBoxThreads = 256;
+constexpr int kBoxMaxBlocks = 64;
+constexpr int kRankWaves = 16;  // waves that share the comparisons of 64 locations
+
+__host__ __device__ inline int box_blocks(int64_t n)
+{
+    const int64_t b = n / kBoxThreads + 1;
+    return (int)(b < kBoxMaxBlocks ? b : kBoxMaxBlocks);
+}
+
+// block b's bounding box of locations b T + t, b T + t + G T, ... (T threads,
+// G blocks) into box[b][0..d) (low) and box[b][d..2d) (high); fmin/fmax skip
+// NaN coordinates
+__global__ void __launch_bounds__(kBoxThreads)
+    order_box_kernel(int64_t n, int d, const double* __restrict__ x, int64_t ldx,
+                     double* __restrict__ box)
+{
+    __shared__ double wlo[kBoxThreads / kWave], whi[kBoxThreads / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), wv = t / kWave;
+    for (int dd = 0; dd < d; ++dd) {
+        double a = INFINITY, b = -INFINITY;
+        for (int64_t i = (int64_t)blockIdx.x * kBoxThreads + t; i < n;
+             i += (int64_t)gridDim.x * kBoxThreads) {
+            const double v = x[i * ldx + dd];
+            a = fmin(a, v);
+            b = fmax(b, v);
+        }
+        for (int m = 32; m >= 1; m >>= 1) {
+            a = fmin(a, __shfl_xor(a, m, kWave));
+            b = fmax(b, __shfl_xor(b, m, kWave));
+        }
+        if (lane == 0) {
+            wlo[wv] = a;
+            whi[wv] = b;
+        }
+        __syncthreads();
+        if (t == 0) {
+            for (int q = 1; q < kBoxThreads / kWave; ++q) {
+                a = fmin(a, wlo[q]);
+                b = fmax(b, whi[q]);
+            }
+            box[(int64_t)blockIdx.x * 2 * d + dd] = a;
+            box[(int64_t)blockIdx.x * 2 * d + d + dd] = b;
+        }
+        __syncthreads();
+    }
+}
+
+// the key of each location in the box of all blocks (at most 64 of them: one
+// per lane, wave w takes dimensions w, w + 4)
+__global__ void __launch_bounds__(kBoxThreads)
+    order_key_kernel(int64_t n, int d, const double* __restrict__ x, int64_t ldx, int blocks,
+                     const double* __restrict__ box, uint32_t* __restrict__ key)
+{
+    __shared__ double lo[MDS_MAX_DIM], hi[MDS_MAX_DIM];
+    const int t = threadIdx.x, lane = t & (kWave - 1);
+    for (int dd = t / kWave; dd < d; dd += kBoxThreads / kWave) {
+        const double* p = box + (int64_t)min(lane, blocks - 1) * 2 * d + dd;
+        double a = p[0], b = p[d];
+        for (int m = 32; m >= 1; m >>= 1) {
+            a = fmin(a, __shfl_xor(a, m, kWave));
+            b = fmax(b, __shfl_xor(b, m, kWave));
+        }
+        if (lane == 0) {
+            lo[dd] = a;
+            hi[dd] = b;
+        }
+    }
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kBoxThreads + t;
+    if (i < n) key[i] = point_key(x + i * ldx, d, lo, hi);
+}
+
+// perm[rank of i] = i for 64 locations i (lane = location): wave w counts over
+// the w-th share of the locations j, whose keys are uniform (scalar loads).
+// Ahead of the block's own locations an equal key counts (its index is
+// smaller), behind them it does not; among them the index decides.
+__global__ void __launch_bounds__(kWave * kRankWaves)
+    order_rank_kernel(int n, const uint32_t* __restrict__ key, int64_t* __restrict__ perm)
+{
+    __shared__ int part[kRankWaves][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int i0 = blockIdx.x * kWave, i = i0 + lane;
+    const uint32_t k = key[min(i, n - 1)];
+    const int share = (n + kRankWaves - 1) / kRankWaves;
+    const int j0 = min(n, w * share), j1 = min(n, j0 + share);
+    const int b0 = min(j1, max(j0, i0)), b1 = min(j1, max(j0, i0 + kWave));
+    int c = 0;
+#pragma unroll 16
+    for (int j = j0; j < b0; ++j) c += key[j] <= k ? 1 : 0;
+    for (int j = b0; j < b1; ++j) c += (key[j] < k || (key[j] == k && j < i)) ? 1 : 0;
+#pragma unroll 16
+    for (int j = b1; j < j1; ++j) c += key[j] < k ? 1 : 0;
+    part[w][lane] = c;
+    __syncthreads();
+    if (w != 0 || i >= n) return;
+    int rank = 0;
+#pragma unroll
+    for (int q = 0; q < kRankWaves; ++q) rank += part[q][lane];
+    perm[rank] = (int64_t)i;
+}
+
+// ---- by a radix sort in one work-group
 
 __global__ void __launch_bounds__(kOrdThreads)
     order_kernel(int64_t n, int d, const double* __restrict__ x, int64_t ldx, uint32_t* key0,
@@ -198,6 +312,24 @@ hipError_t launch_order(int64_t n, int d, const double* x, int64_t ldx, int64_t*
     if (n == 0) return hipSuccess;
     const size_t one = align_up((size_t)n * sizeof(uint32_t), 256);
     char* base = static_cast<char*>(ws);
+    if (n <= kRankMaxN) {
+        // keys in the first section, the boxes (128 bytes a block of 256
+        // locations at most) in the three behind it
+        uint32_t* key = reinterpret_cast<uint32_t*>(base);
+        double* box = reinterpret_cast<double*>(base + one);
+        const int blocks = box_blocks(n);
+        hipLaunchKernelGGL(order_box_kernel, dim3(blocks), dim3(kBoxThreads), 0, s, n, d, x, ldx,
+                           box);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(order_key_kernel, dim3((unsigned)((n + kBoxThreads - 1) / kBoxThreads)),
+                           dim3(kBoxThreads), 0, s, n, d, x, ldx, blocks, box, key);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(order_rank_kernel, dim3((unsigned)((n + kWave - 1) / kWave)),
+                           dim3(kWave * kRankWaves), 0, s, (int)n, key, perm);
+        return hipGetLastError();
+    }
     uint32_t* k0 = reinterpret_cast<uint32_t*>(base);
     uint32_t* k1 = reinterpret_cast<uint32_t*>(base + one);
     uint32_t* i0 = reinterpret_cast<uint32_t*>(base + 2 * one);
