@@ -421,9 +421,25 @@ __global__ void zero_i64_kernel(int64_t* p)
     if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
 }
 
+// adds a work-group's observed pairs to the count: one integer atomic per
+// work-group (integer addition: the count does not depend on the order)
+template <int T>
+__device__ __forceinline__ void add_observed(int obs, unsigned long long* count)
+{
+    __shared__ int wsum[T / kWave];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) obs += __shfl_xor(obs, m, kWave);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / kWave] = obs;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int tot = 0;
+        for (int q = 0; q < T / kWave; ++q) tot += wsum[q];
+        if (tot) atomicAdd(count, (unsigned long long)tot);
+    }
+}
+
 // One work-group per row i: converts, folds the mask and NaN into NaN, and
-// counts the observed pairs i > j of the row; one integer atomic per row
-// (integer addition: the count does not depend on the order).
+// counts the observed pairs i > j of the row.
 template <typename S, typename O>
 __global__ void __launch_bounds__(256)
     prepare_kernel(const S* src, int64_t ld_src, const uint8_t* mask, int64_t ld_mask, O* out,
@@ -458,18 +474,83 @@ __global__ void __launch_bounds__(256)
             obs += (!miss && j < i) ? 1 : 0;
         }
     }
-    if (count) {
-        __shared__ int wsum[256 / kWave];
+    if (count) add_observed<256>(obs, count);
+}
+
+// The relabelling prepare where a row of Y fits the LDS: the work-group reads
+// row perm[i] of the source and its mask in order, converted and with missing
+// entries as NaN, into LDS and gathers the output row from there.  The direct
+// gather of prepare_kernel issues one request per lane and cache line; this
+// reads every line once.  kPrepUnroll loads in flight per lane.
+// N = 5392, FP64 with a mask: 363 -> 126 us (493 MB, 3.9 of the 4.9 TB/s a
+// large copy reaches).
+constexpr int kPrepThreads = 1024;
+constexpr int kPrepUnroll = 4;
+constexpr size_t kPrepMaxLds = 64 * 1024;
+
+template <typename S, typename O>
+__global__ void __launch_bounds__(kPrepThreads)
+    prepare_relabel_kernel(const S* __restrict__ src, int64_t ld_src,
+                           const uint8_t* __restrict__ mask, int64_t ld_mask, O* __restrict__ out,
+                           int64_t ldy, int n, const int64_t* __restrict__ perm,
+                           unsigned long long* count)
+{
+    extern __shared__ double prep_lds[];
+    O* row = reinterpret_cast<O*>(prep_lds);
+    const int i = blockIdx.x, t = threadIdx.x;
+    const int64_t si = perm[i];
+    const bool rok = si >= 0 && si < n;  // an index out of range reads as missing pairs
+    const S* srow = src + (rok ? si : 0) * ld_src;
+    const uint8_t* mrow = mask ? mask + (rok ? si : 0) * ld_mask : nullptr;
+    for (int j0 = t; j0 < n; j0 += kPrepUnroll * kPrepThreads) {
+        S v[kPrepUnroll];
+        uint8_t m[kPrepUnroll];
 #pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) obs += __shfl_xor(obs, m, kWave);
-        if ((threadIdx.x & 63) == 0) wsum[threadIdx.x / kWave] = obs;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int tot = 0;
-            for (int q = 0; q < 256 / kWave; ++q) tot += wsum[q];
-            if (tot) atomicAdd(count, (unsigned long long)tot);
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            const int j = min(j0 + u * kPrepThreads, n - 1);
+            v[u] = srow[j];
+            m[u] = mrow ? mrow[j] : (uint8_t)0;
+        }
+#pragma unroll
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            const int j = j0 + u * kPrepThreads;
+            if (j < n) row[j] = (!rok || m[u] != 0 || isnan(v[u])) ? (O)NAN : (O)v[u];
         }
     }
+    __syncthreads();
+    O* orow = out + (int64_t)i * ldy;
+    int obs = 0;
+    for (int j0 = t; j0 < n; j0 += kPrepUnroll * kPrepThreads) {
+        int64_t sj[kPrepUnroll];
+#pragma unroll
+        for (int u = 0; u < kPrepUnroll; ++u) sj[u] = perm[min(j0 + u * kPrepThreads, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kPrepUnroll; ++u) {
+            const int j = j0 + u * kPrepThreads;
+            if (j < n) {
+                const O v = (sj[u] >= 0 && sj[u] < n) ? row[sj[u]] : (O)NAN;
+                orow[j] = v;
+                obs += (j < i && !isnan(v)) ? 1 : 0;
+            }
+        }
+    }
+    if (count) add_observed<kPrepThreads>(obs, count);
+}
+
+template <typename S, typename O>
+void launch_prepare_t(const S* src, int64_t ld_src, const uint8_t* mask, int64_t ld_mask, O* out,
+                      int64_t ldy, int64_t n, const int64_t* perm, unsigned long long* count,
+                      hipStream_t s)
+{
+    const size_t lds = (size_t)n * sizeof(O);
+    // short rows leave a work-group of 1024 mostly idle: below 512 columns the
+    // direct gather is as fast
+    if (perm && n >= 512 && lds <= kPrepMaxLds)
+        hipLaunchKernelGGL((prepare_relabel_kernel<S, O>), dim3((unsigned)n), dim3(kPrepThreads),
+                           lds, s, src, ld_src, mask, ld_mask, out, ldy, (int)n, perm, count);
+    else
+        hipLaunchKernelGGL((prepare_kernel<S, O>), dim3((unsigned)n), dim3(256), 0, s, src, ld_src,
+                           mask, ld_mask, out, ldy, n, perm, count);
 }
 
 hipError_t launch_prepare(const void* src, int sdt, int64_t ld_src, const uint8_t* mask,
@@ -482,20 +563,15 @@ hipError_t launch_prepare(const void* src, int sdt, int64_t ld_src, const uint8_
         if (e != hipSuccess) return e;
     }
     if (n == 0) return hipSuccess;
-    const dim3 grid((unsigned)n);
     unsigned long long* c = reinterpret_cast<unsigned long long*>(count);
     if (sdt == 0 && odt == 0)
-        hipLaunchKernelGGL((prepare_kernel<double, double>), grid, dim3(256), 0, s,
-                           (const double*)src, ld_src, mask, ld_mask, (double*)out, ldy, n, perm, c);
+        launch_prepare_t((const double*)src, ld_src, mask, ld_mask, (double*)out, ldy, n, perm, c, s);
     else if (sdt == 0 && odt == 1)
-        hipLaunchKernelGGL((prepare_kernel<double, float>), grid, dim3(256), 0, s,
-                           (const double*)src, ld_src, mask, ld_mask, (float*)out, ldy, n, perm, c);
+        launch_prepare_t((const double*)src, ld_src, mask, ld_mask, (float*)out, ldy, n, perm, c, s);
     else if (sdt == 1 && odt == 0)
-        hipLaunchKernelGGL((prepare_kernel<float, double>), grid, dim3(256), 0, s,
-                           (const float*)src, ld_src, mask, ld_mask, (double*)out, ldy, n, perm, c);
+        launch_prepare_t((const float*)src, ld_src, mask, ld_mask, (double*)out, ldy, n, perm, c, s);
     else
-        hipLaunchKernelGGL((prepare_kernel<float, float>), grid, dim3(256), 0, s,
-                           (const float*)src, ld_src, mask, ld_mask, (float*)out, ldy, n, perm, c);
+        launch_prepare_t((const float*)src, ld_src, mask, ld_mask, (float*)out, ldy, n, perm, c, s);
     return hipGetLastError();
 }
 
