@@ -19,27 +19,70 @@ constexpr int kRowThreads = 256;
 constexpr int kScanThreads = 1024;
 constexpr int kPartThreads = 256;
 
-template <typename S>
-__device__ __forceinline__ bool heldout_pair(const S* y, int64_t ld_y, const uint8_t* missing,
-                                             int64_t ld_m, const uint8_t* heldout, int64_t ld_h,
-                                             int64_t i, int64_t j)
+// The compaction passes walk a row in rounds of four columns per thread: one
+// word of held-out bytes and one of mask bytes, loaded together, then y of the
+// columns they keep.  (One byte per lane and load made them bound by vector
+// memory instructions.)  They read the lower triangles of both masks and most
+// lines of y's.  N = 5392, FP64, 10% held out, a mask: count 58 -> 46 us (it
+// runs beside the write-back of the prepared Y), fill 61 -> 30 us.
+// bytes j .. j+3 of a row as a word, byte 0 lowest; columns at or past `end`
+// read as 0.  `wide`: the row starts at a multiple of four bytes (and then a
+// word inside its n columns is one load).
+__device__ __forceinline__ uint32_t row_word(const uint8_t* row, int j, int end, int n, bool wide)
 {
-    if (heldout[i * ld_h + j] == 0) return false;
-    if (missing && missing[i * ld_m + j] != 0) return false;
-    return !isnan(y[i * ld_y + j]);
+    if (wide && j + 3 < n) {
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(row + j);
+        const int left = end - j;
+        return left >= 4 ? v : (left <= 0 ? 0u : v & (0xffffffffu >> (32 - 8 * left)));
+    }
+    uint32_t v = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+        if (j + b < end) v |= (uint32_t)row[j + b] << (8 * b);
+    return v;
+}
+
+struct HeldoutRows {
+    const uint8_t* missing;  // NULL: no mask
+    int64_t ld_m;
+    const uint8_t* heldout;
+    int64_t ld_h;
+    int n;
+    bool wide_m, wide_h;  // every row starts at a multiple of four bytes
+};
+
+// keep[b]: whether pair (i, j0 + b) is held out, j0 + b below i; yv[b]: its y
+template <typename S>
+__device__ __forceinline__ void heldout_pairs(const S* __restrict__ yrow, const HeldoutRows& r,
+                                              int i, int j0, bool (&keep)[4], S (&yv)[4])
+{
+    const uint32_t h = row_word(r.heldout + i * r.ld_h, j0, i, r.n, r.wide_h);
+    const uint32_t m =
+        r.missing ? row_word(r.missing + i * r.ld_m, j0, i, r.n, r.wide_m) : 0u;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        keep[b] = ((h >> (8 * b)) & 0xffu) != 0 && ((m >> (8 * b)) & 0xffu) == 0;
+        yv[b] = keep[b] ? yrow[j0 + b] : (S)0;
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) keep[b] = keep[b] && !isnan(yv[b]);
 }
 
 // held-out pairs of row i (j < i)
 template <typename S>
 __global__ void __launch_bounds__(kRowThreads)
-    heldout_count_kernel(const S* __restrict__ y, int64_t ld_y, const uint8_t* __restrict__ missing,
-                         int64_t ld_m, const uint8_t* __restrict__ heldout, int64_t ld_h,
+    heldout_count_kernel(const S* __restrict__ y, int64_t ld_y, HeldoutRows r,
                          int64_t* __restrict__ row_count)
 {
-    const int64_t i = blockIdx.x;
+    const int i = blockIdx.x;
     int c = 0;
-    for (int64_t j = threadIdx.x; j < i; j += kRowThreads)
-        c += heldout_pair(y, ld_y, missing, ld_m, heldout, ld_h, i, j) ? 1 : 0;
+    for (int j0 = 4 * threadIdx.x; j0 < i; j0 += 4 * kRowThreads) {
+        bool keep[4];
+        S yv[4];
+        heldout_pairs(y + i * ld_y, r, i, j0, keep, yv);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) c += keep[b] ? 1 : 0;
+    }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) c += __shfl_xor(c, m, kWave);
     __shared__ int wsum[kRowThreads / kWave];
@@ -52,30 +95,35 @@ __global__ void __launch_bounds__(kRowThreads)
     }
 }
 
-// in place: row_count -> exclusive row offsets; row n holds the total
+// in place: row_count -> exclusive row offsets; row n holds the total.  Each
+// thread sums its chunk of rows, the chunk sums are scanned by lane shifts
+// within waves and then over the waves
 __global__ void __launch_bounds__(kScanThreads)
     row_scan_kernel(int64_t n, int64_t* __restrict__ rows, int64_t* __restrict__ total)
 {
-    __shared__ int64_t part[kScanThreads];
-    const int t = threadIdx.x;
+    __shared__ int64_t wsum[kScanThreads / kWave];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
     const int64_t chunk = (n + kScanThreads - 1) / kScanThreads;
     const int64_t r0 = min(n, (int64_t)t * chunk), r1 = min(n, r0 + chunk);
     int64_t s = 0;
+#pragma unroll 8
     for (int64_t r = r0; r < r1; ++r) s += rows[r];
-    part[t] = s;
-    __syncthreads();
-    if (t == 0) {
-        int64_t run = 0;
-        for (int q = 0; q < kScanThreads; ++q) {
-            const int64_t v = part[q];
-            part[q] = run;
-            run += v;
-        }
-        rows[n] = run;
-        *total = run;
+    int64_t inc = s;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t v = __shfl_up(inc, o, kWave);
+        if (lane >= o) inc += v;
     }
+    if (lane == kWave - 1) wsum[w] = inc;
     __syncthreads();
-    int64_t run = part[t];
+    int64_t run = inc - s, all = 0;
+    for (int q = 0; q < kScanThreads / kWave; ++q) {
+        run += q < w ? wsum[q] : 0;
+        all += wsum[q];
+    }
+    if (t == 0) {
+        rows[n] = all;
+        *total = all;
+    }
     for (int64_t r = r0; r < r1; ++r) {
         const int64_t v = rows[r];
         rows[r] = run;
@@ -83,37 +131,51 @@ __global__ void __launch_bounds__(kScanThreads)
     }
 }
 
-// writes the held-out pairs of row i at its offset, in column order
+// writes the held-out pairs of row i at its offset, in column order: the
+// columns of a round are ordered by (wave, lane, byte)
 template <typename S>
 __global__ void __launch_bounds__(kRowThreads)
-    heldout_fill_kernel(const S* __restrict__ y, int64_t ld_y, const uint8_t* __restrict__ missing,
-                        int64_t ld_m, const uint8_t* __restrict__ heldout, int64_t ld_h,
+    heldout_fill_kernel(const S* __restrict__ y, int64_t ld_y, HeldoutRows r,
                         const int64_t* __restrict__ row_off, int64_t capacity,
                         int32_t* __restrict__ pi, int32_t* __restrict__ pj, double* __restrict__ py)
 {
-    const int64_t i = blockIdx.x;
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    __shared__ int wcount[kRowThreads / kWave];
+    constexpr int W = kRowThreads / kWave;
+    const int i = blockIdx.x, t = threadIdx.x;
+    const int lane = t & (kWave - 1), w = t / kWave;
+    const uint64_t below = (1ull << lane) - 1ull;
+    __shared__ int wcount[W];
     int64_t base = row_off[i];
-    for (int64_t j0 = 0; j0 < i; j0 += kRowThreads) {
-        const int64_t j = j0 + threadIdx.x;
-        const bool keep = j < i && heldout_pair(y, ld_y, missing, ld_m, heldout, ld_h, i, j);
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
-        const int before = __builtin_popcountll(mask & ((1ull << lane) - 1ull));
-        if (lane == 0) wcount[w] = __builtin_popcountll(mask);
+    for (int r0 = 0; r0 < i; r0 += 4 * kRowThreads) {
+        const int j0 = r0 + 4 * t;
+        bool keep[4];
+        S yv[4];
+        heldout_pairs(y + i * ld_y, r, i, j0, keep, yv);
+        int all = 0, before = 0;  // kept pairs of the wave, and of its lanes below this one
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep[b]);
+            all += __builtin_popcountll(mask);
+            before += __builtin_popcountll(mask & below);
+        }
+        if (lane == 0) wcount[w] = all;
         __syncthreads();
-        int wbase = 0, all = 0;
-        for (int q = 0; q < kRowThreads / kWave; ++q) {
-            wbase += (q < w) ? wcount[q] : 0;
-            all += wcount[q];
+        int mine = 0, run = 0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            mine = q == w ? run : mine;
+            run += wcount[q];
         }
-        const int64_t k = base + wbase + before;
-        if (keep && k < capacity) {
-            pi[k] = (int32_t)i;
-            pj[k] = (int32_t)j;
-            py[k] = (double)y[i * ld_y + j];
+        int64_t k = base + mine + before;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            if (keep[b] && k < capacity) {
+                pi[k] = i;
+                pj[k] = j0 + b;
+                py[k] = (double)yv[b];
+            }
+            k += keep[b] ? 1 : 0;
         }
-        base += all;
+        base += run;
         __syncthreads();
     }
 }
@@ -274,17 +336,27 @@ __global__ void __launch_bounds__(kLpdMaxParts)
 
 }  // namespace
 
+namespace {
+HeldoutRows heldout_rows(const uint8_t* missing, int64_t ld_m, const uint8_t* heldout,
+                         int64_t ld_h, int64_t n)
+{
+    auto wide = [](const uint8_t* p, int64_t ld) { return ((uintptr_t)p | (uintptr_t)ld) % 4 == 0; };
+    return {missing, ld_m, heldout, ld_h, (int)n, wide(missing, ld_m), wide(heldout, ld_h)};
+}
+}  // namespace
+
 hipError_t launch_heldout_count(const void* y, int dt, int64_t ld_y, const uint8_t* missing,
                                 int64_t ld_m, const uint8_t* heldout, int64_t ld_h, int64_t n,
                                 int64_t* rows, int64_t* total, hipStream_t s)
 {
     if (n > 0) {
+        const HeldoutRows r = heldout_rows(missing, ld_m, heldout, ld_h, n);
         if (dt == 0)
             hipLaunchKernelGGL((heldout_count_kernel<double>), dim3((unsigned)n), dim3(kRowThreads),
-                               0, s, (const double*)y, ld_y, missing, ld_m, heldout, ld_h, rows);
+                               0, s, (const double*)y, ld_y, r, rows);
         else
             hipLaunchKernelGGL((heldout_count_kernel<float>), dim3((unsigned)n), dim3(kRowThreads),
-                               0, s, (const float*)y, ld_y, missing, ld_m, heldout, ld_h, rows);
+                               0, s, (const float*)y, ld_y, r, rows);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -298,14 +370,13 @@ hipError_t launch_heldout_fill(const void* y, int dt, int64_t ld_y, const uint8_
                                double* py, hipStream_t s)
 {
     if (n == 0) return hipSuccess;
+    const HeldoutRows r = heldout_rows(missing, ld_m, heldout, ld_h, n);
     if (dt == 0)
         hipLaunchKernelGGL((heldout_fill_kernel<double>), dim3((unsigned)n), dim3(kRowThreads), 0,
-                           s, (const double*)y, ld_y, missing, ld_m, heldout, ld_h, rows, capacity,
-                           pi, pj, py);
+                           s, (const double*)y, ld_y, r, rows, capacity, pi, pj, py);
     else
         hipLaunchKernelGGL((heldout_fill_kernel<float>), dim3((unsigned)n), dim3(kRowThreads), 0,
-                           s, (const float*)y, ld_y, missing, ld_m, heldout, ld_h, rows, capacity,
-                           pi, pj, py);
+                           s, (const float*)y, ld_y, r, rows, capacity, pi, pj, py);
     return hipGetLastError();
 }
 
