@@ -12,8 +12,8 @@ Everything is computed here from the mathematics with mpmath (50 digits):
   towards the minimax fit in relative error).  Z is where exp(-z^2) leaves the
   range of the format (FP64: z^2 > 745; FP32: z^2 > 104), beyond which the
   product exp(-z^2) erfcx(z) is 0 whatever erfcx is.  A second, shorter FP64
-  rational covers [2.1, 6.6] only (t = z sqrt 2 from 2.97 to 9.33), for the
-  wavefronts whose pairs all lie at t >= 3.
+  rational covers [2.1, 6.6] only (t = z sqrt 2 from 2.97 to 9.33); the kernels
+  no longer use it, its table stays for the test that checks it.
 * The FP64 sweep's near pairs need q = 1 - Phi(t) = e R(t), e = exp(-t^2/2)
   and R(t) = erfcx(t/sqrt 2)/2, to an absolute error only (q enters as 1 - q),
   so R is fitted as P(t)/Q(t), Q(0) = 1, with weight e on [0, 9] (9 the sweep's

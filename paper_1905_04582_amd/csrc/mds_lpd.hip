@@ -186,21 +186,46 @@ __global__ void __launch_bounds__(kRowThreads)
 // acc[2k+1] = sum of exp(l - largest)); `first` starts the sums with the
 // first draw.  The state stays in registers across the draws, so a call with
 // S draws reads and writes it once instead of S times.  Each thread takes
-// lpd_pairs(S == 1) pairs (one block covers 256 times that many consecutive pairs,
-// lane-strided so every load is coalesced), so ln sigma and 1/sigma are
-// formed once per thread and draw.  A wavefront whose pairs all have
-// delta/sigma >= 9 takes ln Phi = 0 (|ln Phi(t)| < 2.3e-19 there, far below
-// the rounding of l).  The arithmetic of a draw does not depend on how the
-// draws are grouped into calls: S calls of one draw and one call of S draws
-// give the same bits.
-// Pairs per thread (even: the special functions take two pairs at a time).
-// One draw per pass streams the pair list and the state: two pairs per thread
-// give twice the work-groups to hide memory latency (7% faster than four at
-// 1.24 M pairs).  Several draws per pass are arithmetic-bound: four pairs per
-// thread share ln sigma and 1/sigma of each draw (6% faster than two).
-constexpr int lpd_pairs(bool one) { return one ? 2 : 4; }
-static_assert(lpd_pairs(true) % 2 == 0 && lpd_pairs(false) % 2 == 0, "pairs per thread");
-constexpr int kLpdThreads = 256;
+// kLpdPairs pairs (one block covers 128 consecutive pairs, lane-strided so every load is
+// coalesced); ln sigma and 1/sigma of a chunk of
+// draws are formed once per block, in LDS.  A pair with delta/sigma >= 9 takes
+// ln Phi = 0 (|ln Phi(t)| < 2.3e-19 there, far below the rounding of l), and a
+// wavefront skips the terms when every pair does.  The arithmetic of a draw
+// does not depend on how the draws are grouped into calls: S calls of one draw
+// and one call of S draws give the same bits.
+//
+// Several draws per pass are bound by vector instructions (129 per pair
+// and draw with the short forms of mds_math.h; the library's exp, log and sqrt
+// and a relative ln Phi took 190), one draw per pass by the pair list and the
+// state it streams.  1.45 M pairs, D = 2, ten draws and the finalize: 102 -> 85
+// us (73% of the issue slots busy).
+//
+// Two pairs per thread (the special functions take two at a time) and blocks of
+// one wave: the most work-groups, so that small lists fill the chip (2800
+// locations, 0.39 M pairs, ten draws: 38.8 -> 32.0 us against blocks of 256
+// threads with four pairs) and large ones end evenly (1.45 M pairs: 86.6 -> 85.3
+// us; six dimensions, twelve draws, 2.9 M pairs: 215 -> 200 us).
+constexpr int kLpdThreads = kWave;
+constexpr int kLpdPairs = 2;
+constexpr int kLpdDrawChunk = 64;  // draws whose constants a block holds at a time
+
+struct DrawConst {
+    double inv_sigma;
+    double c2;  // -log2(e) / (2 sigma^2)
+    double c0;  // -ln(sqrt(2 pi) sigma)
+};
+
+// sqrt(s2): s2 / sqrt(s2) and one correction by its own residual, which leaves
+// the final rounding (z = (y - delta)/sigma magnifies an error of delta); the
+// rare values out of its range (infinite, NaN) go through the library's
+__device__ __forceinline__ double lpd_distance(double s2)
+{
+    const double rs = rsqrt_f64(fmax(s2, 2.2250738585072014e-308));
+    double delta = s2 * rs;
+    delta = fma(fma(-delta, delta, s2), 0.5 * rs, delta);
+    if (__builtin_amdgcn_ballot_w64(!(s2 < 1e300))) delta = s2 < 1e300 ? delta : sqrt(s2);
+    return delta;
+}
 
 template <int D, bool ONE>
 __global__ void __launch_bounds__(kLpdThreads)
@@ -210,82 +235,90 @@ __global__ void __launch_bounds__(kLpdThreads)
                           int32_t n_draws, double* __restrict__ acc, int first)
 {
     constexpr double kLnSqrt2Pi = 0.91893853320467274178;
-    constexpr int kLpdPairs = lpd_pairs(ONE);
-    const int64_t base = (int64_t)blockIdx.x * (kLpdThreads * kLpdPairs) + threadIdx.x;
-    int64_t ii[kLpdPairs], jj[kLpdPairs];
-    double yv[kLpdPairs], mx[kLpdPairs], sm[kLpdPairs];
+    constexpr int T = kLpdThreads, P = kLpdPairs;
+    static_assert(P % 2 == 0 && T >= kLpdDrawChunk, "pairs and threads");
+    __shared__ DrawConst dc[ONE ? 1 : kLpdDrawChunk];
+    const int64_t base = (int64_t)blockIdx.x * (T * P) + threadIdx.x;
+    int64_t ii[P], jj[P];
+    double yv[P], mx[P], sm[P];
 #pragma unroll
-    for (int u = 0; u < kLpdPairs; ++u) {
-        const int64_t k = base + (int64_t)u * kLpdThreads;
+    for (int u = 0; u < P; ++u) {
+        const int64_t k = base + (int64_t)u * T;
         // a lane past the end works on the last pair and stores nothing
         const int64_t kk = k < m ? k : m - 1;
-        ii[u] = pi[kk];
-        jj[u] = pj[kk];
+        ii[u] = pi[kk] * ldx;
+        jj[u] = pj[kk] * ldx;
         yv[u] = py[kk];
         mx[u] = first ? 0.0 : acc[2 * kk];
         sm[u] = first ? 0.0 : acc[2 * kk + 1];
     }
-    // ONE: a single draw, with the loop known to run once (same arithmetic)
+    // ONE: a single draw, with the loops known to run once (same arithmetic)
     const int32_t draws = ONE ? 1 : n_draws;
     const tab64_ptr tb = tab64();
-    for (int s = 0; s < draws; ++s) {
-        const double sigma = sigmas[s];
-        const double inv_sigma = 1.0 / sigma;
-        const double c0 = -kLnSqrt2Pi - log(sigma);
-        const double* x = xs + (int64_t)s * xstride;
-        const bool start = first && s == 0;
-        double z[kLpdPairs], t[kLpdPairs];
-#pragma unroll
-        for (int u = 0; u < kLpdPairs; ++u) {
-            double s2 = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                const double diff = x[ii[u] * ldx + d] - x[jj[u] * ldx + d];
-                s2 = fma(diff, diff, s2);
-            }
-            const double delta = sqrt(s2);
-            z[u] = (yv[u] - delta) * inv_sigma;
-            t[u] = delta * inv_sigma;
+    for (int s0 = 0; s0 < draws; s0 += kLpdDrawChunk) {
+        const int chunk = ONE ? 1 : min(draws - s0, kLpdDrawChunk);
+        __syncthreads();
+        if ((int)threadIdx.x < chunk) {
+            const double sigma = sigmas[s0 + threadIdx.x];
+            const double inv = 1.0 / sigma;
+            dc[threadIdx.x] = {inv, -0.5 * kLog2e * inv * inv, -kLnSqrt2Pi - log(sigma)};
         }
-        // ln Phi(t) two pairs at a time: skipped by the whole wave when every
-        // t is past the skip point (9), in its far-range forms when every t
-        // is at or past kFarT, else in its full-range forms
+        __syncthreads();
+        for (int sc = 0; sc < chunk; ++sc) {
+            const DrawConst c = dc[sc];
+            const double* x = xs + (int64_t)(s0 + sc) * xstride;
+            const bool start = first && s0 + sc == 0;
+            double s2[P];
 #pragma unroll
-        for (int u = 0; u < kLpdPairs; u += 2) {
-            double lp0 = 0.0, lp1 = 0.0, m0, m1;
-            if (__builtin_amdgcn_ballot_w64(t[u] < 9.0) | __builtin_amdgcn_ballot_w64(t[u + 1] < 9.0)) {
-                if ((__builtin_amdgcn_ballot_w64(t[u] < kFarT) |
-                     __builtin_amdgcn_ballot_w64(t[u + 1] < kFarT)) == 0)
-                    trunc_terms2_far_f64(t[u], t[u + 1], lp0, m0, lp1, m1, tb);
-                else
-                    trunc_terms2_f64(t[u], t[u + 1], lp0, m0, lp1, m1, tb);
+            for (int u = 0; u < P; ++u) {
+                s2[u] = 0.0;
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const double diff = x[ii[u] + d] - x[jj[u] + d];
+                    s2[u] = fma(diff, diff, s2[u]);
+                }
             }
-            const double lp[2] = {lp0, lp1};
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int v = u + h;
-                const double l = c0 - 0.5 * z[v] * z[v] - lp[h];
-                // running log-sum-exp: one exp of -|l - largest| serves both
-                // cases
+            for (int u = 0; u < P; u += 2) {
+                const double da = lpd_distance(s2[u]), db = lpd_distance(s2[u + 1]);
+                const double ta = da * c.inv_sigma, tb2 = db * c.inv_sigma;
+                const bool na = ta < 9.0, nb = tb2 < 9.0;
+                double l[2] = {0.0, 0.0};
+                if (__builtin_amdgcn_ballot_w64(na) | __builtin_amdgcn_ballot_w64(nb))
+                    neg_ln_phi2_f64(s2[u], s2[u + 1], ta, tb2, na, nb, c.c2, tb, l[0], l[1]);
+                const double za = (yv[u] - da) * c.inv_sigma;
+                const double zb = (yv[u + 1] - db) * c.inv_sigma;
+                l[0] += fma(-0.5 * za, za, c.c0);
+                l[1] += fma(-0.5 * zb, zb, c.c0);
                 if (start) {
-                    mx[v] = l;
-                    sm[v] = 1.0;
-                } else {
-                    const double dl = l - mx[v];
-                    const double e = exp(-fabs(dl));
-                    if (dl > 0.0) {
-                        sm[v] = sm[v] * e + 1.0;
-                        mx[v] = l;
-                    } else {
-                        sm[v] += e;
-                    }
+                    mx[u] = l[0];
+                    mx[u + 1] = l[1];
+                    sm[u] = sm[u + 1] = 1.0;
+                    continue;
+                }
+                // running log-sum-exp: one exp of -|l - largest| serves both
+                // cases; arguments out of the short form's range (and NaN) go
+                // through the library's
+                const double dl[2] = {l[0] - mx[u], l[1] - mx[u + 1]};
+                double e[2];
+                exp2_neg_f64(-fabs(dl[0]), -fabs(dl[1]), tb, e[0], e[1]);
+                if (__builtin_amdgcn_ballot_w64(!(fabs(dl[0]) < 700.0)) |
+                    __builtin_amdgcn_ballot_w64(!(fabs(dl[1]) < 700.0))) {
+                    e[0] = fabs(dl[0]) < 700.0 ? e[0] : exp(-fabs(dl[0]));
+                    e[1] = fabs(dl[1]) < 700.0 ? e[1] : exp(-fabs(dl[1]));
+                }
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bool up = dl[h] > 0.0;
+                    sm[u + h] = fma(up ? sm[u + h] : 1.0, e[h], up ? 1.0 : sm[u + h]);
+                    mx[u + h] = up ? l[h] : mx[u + h];
                 }
             }
         }
     }
 #pragma unroll
-    for (int u = 0; u < kLpdPairs; ++u) {
-        const int64_t k = base + (int64_t)u * kLpdThreads;
+    for (int u = 0; u < P; ++u) {
+        const int64_t k = base + (int64_t)u * T;
         if (k < m) {
             acc[2 * k] = mx[u];
             acc[2 * k + 1] = sm[u];
@@ -386,7 +419,7 @@ hipError_t launch_lpd_accumulate(int64_t m, const int32_t* pi, const int32_t* pj
                                  double* acc, int first, hipStream_t s)
 {
     if (m == 0 || n_draws == 0) return hipSuccess;
-    const int64_t per_block = (int64_t)kLpdThreads * lpd_pairs(n_draws == 1);
+    const int64_t per_block = kLpdThreads * kLpdPairs;
     const dim3 grid((unsigned)((m + per_block - 1) / per_block)), block(kLpdThreads);
 #define MDS_LPD_CASE(DD)                                                                     \
     case DD:                                                                                 \

@@ -10,7 +10,9 @@
 // short polynomial on [0, 1/9], and log1p keeps full relative accuracy as
 // q -> 0.  The two divisions share one reciprocal of (4Q - a)(4Q - 2a).
 // Coefficients come from gen_coeffs.py (mds_coeffs.h).  Every lane runs the
-// same instructions whatever t is: no branches, no lane divergence.
+// same instructions whatever t is: no branches, no lane divergence.  The FP64
+// sweep and the held-out density use shorter forms with an absolute error
+// (further down): what they add ln Phi and phi/Phi to is of order one.
 //
 // The general helpers at the end also cover t < 0 (never reached by the
 // sweeps, where delta >= 0 and sigma > 0) through the log-erfc form
@@ -50,18 +52,11 @@ __device__ __forceinline__ double fma_sc(double acc, double x, double c)
 
 // The FP64 coefficient tables in one constant-memory object, so that one
 // scalar base address reaches every coefficient by an immediate offset.
-// terms of the series -log1p(-q)/q = sum_k q^k/(k+1) kept for q <= 1.5e-3
-// (t >= 2.97): the next term is below 2e-18 of the sum
-constexpr int kLog1pN = 6;
-
 struct CoefTables64 {
     double exp[sizeof(kExpC64) / sizeof(double)];
     double erfcx_p[sizeof(kErfcxP64) / sizeof(double)];
     double erfcx_q[sizeof(kErfcxQ64) / sizeof(double)];
     double atanh[sizeof(kAtanhA64) / sizeof(double)];
-    double erfcx_fp[sizeof(kErfcxFarP64) / sizeof(double)];
-    double erfcx_fq[sizeof(kErfcxFarQ64) / sizeof(double)];
-    double log1p[kLog1pN];  // 1/(k+1), k = 0 .. kLog1pN-1
     double near_p[sizeof(kNearP64) / sizeof(double)];
     double near_q[sizeof(kNearQ64) / sizeof(double)];
     double exp2[sizeof(kExp2C64) / sizeof(double)];
@@ -74,11 +69,6 @@ constexpr CoefTables64 make_tables64()
     for (size_t k = 0; k < sizeof(kErfcxP64) / sizeof(double); ++k) t.erfcx_p[k] = kErfcxP64[k];
     for (size_t k = 0; k < sizeof(kErfcxQ64) / sizeof(double); ++k) t.erfcx_q[k] = kErfcxQ64[k];
     for (size_t k = 0; k < sizeof(kAtanhA64) / sizeof(double); ++k) t.atanh[k] = kAtanhA64[k];
-    for (size_t k = 0; k < sizeof(kErfcxFarP64) / sizeof(double); ++k)
-        t.erfcx_fp[k] = kErfcxFarP64[k];
-    for (size_t k = 0; k < sizeof(kErfcxFarQ64) / sizeof(double); ++k)
-        t.erfcx_fq[k] = kErfcxFarQ64[k];
-    for (int k = 0; k < kLog1pN; ++k) t.log1p[k] = 1.0 / (k + 1);
     for (size_t k = 0; k < sizeof(kNearP64) / sizeof(double); ++k) t.near_p[k] = kNearP64[k];
     for (size_t k = 0; k < sizeof(kNearQ64) / sizeof(double); ++k) t.near_q[k] = kNearQ64[k];
     for (size_t k = 0; k < sizeof(kExp2C64) / sizeof(double); ++k) t.exp2[k] = kExp2C64[k];
@@ -158,8 +148,6 @@ constexpr int kExpN = sizeof(kExpC64) / sizeof(double);
 constexpr int kErfcxPN = sizeof(kErfcxP64) / sizeof(double);
 constexpr int kErfcxQN = sizeof(kErfcxQ64) / sizeof(double);
 constexpr int kAtanhN = sizeof(kAtanhA64) / sizeof(double);
-constexpr int kErfcxFarPN = sizeof(kErfcxFarP64) / sizeof(double);
-constexpr int kErfcxFarQN = sizeof(kErfcxFarQ64) / sizeof(double);
 
 // exp(-t^2/2) for t >= 0; 0 once the value leaves the FP64 range
 __device__ __forceinline__ double exp_neg_half_sq(double t, tab64_ptr tb)
@@ -189,89 +177,15 @@ __device__ __forceinline__ void trunc_terms_f64(double t, double& lnphi, double&
     mills = (4.0 * kInvSqrt2Pi) * (e * Q) * (d1 * rr);
 }
 
-// trunc_terms_f64 for two arguments, sharing every coefficient load; `tb`
-// is the tables' address (tab64())
-__device__ __forceinline__ void trunc_terms2_f64(double t1, double t2, double& lnphi1,
-                                                 double& mills1, double& lnphi2, double& mills2,
-                                                 tab64_ptr tb)
-{
-    const double x1 = fmax(-0.5 * (t1 * t1), -760.0);
-    const double x2 = fmax(-0.5 * (t2 * t2), -760.0);
-    const double k1 = rint(x1 * kLog2e), k2 = rint(x2 * kLog2e);
-    double r1 = fma(k1, -kLn2Head, x1), r2 = fma(k2, -kLn2Head, x2);
-    r1 = fma(k1, -kLn2Tail, r1);
-    r2 = fma(k2, -kLn2Tail, r2);
-    double p1, p2;
-    horner2_tab<kExpN>(tb->exp, r1, r2, p1, p2);
-    const double e1 = ldexp(p1, (int)k1), e2 = ldexp(p2, (int)k2);
-    const double z1 = fmin(t1 * kInvSqrt2, kErfcxZmax64 + 1.0);
-    const double z2 = fmin(t2 * kInvSqrt2, kErfcxZmax64 + 1.0);
-    double P1, P2, Q1, Q2;
-    horner2_tab<kErfcxPN>(tb->erfcx_p, z1, z2, P1, P2);
-    horner2_tab<kErfcxQN>(tb->erfcx_q, z1, z2, Q1, Q2);
-    const double a1 = e1 * P1, a2 = e2 * P2;
-    const double d11 = fma(4.0, Q1, -a1), d12 = fma(4.0, Q2, -a2);
-    const double d21 = d11 - a1, d22 = d12 - a2;
-    const double rr1 = rcp_f64(d11 * d21), rr2 = rcp_f64(d12 * d22);
-    const double s1 = a1 * d21 * rr1, s2 = a2 * d22 * rr2;
-    double A1, A2;
-    horner2_tab<kAtanhN>(tb->atanh, s1 * s1, s2 * s2, A1, A2);
-    lnphi1 = -2.0 * s1 * A1;
-    lnphi2 = -2.0 * s2 * A2;
-    mills1 = (4.0 * kInvSqrt2Pi) * (e1 * Q1) * (d11 * rr1);
-    mills2 = (4.0 * kInvSqrt2Pi) * (e2 * Q2) * (d12 * rr2);
-}
-
-// The same two pairs of values when both t lie at or past kFarT (up to the
-// rounding of the caller's test, t >= 2.97): q = 1 - Phi(t) = exp(-t^2/2)
-// erfcx(t/sqrt 2)/2 <= 1.5e-3 from the far-range rational, ln Phi = log1p(-q)
-// by its series in q (kLog1pN terms), and phi/Phi = phi(t) / (1 - q) by the
-// geometric series (terms to q^6, the next below 1.2e-17).  z is capped at
-// the top of the fit range: past it exp(-t^2/2) < 1e-18, and the values are
-// negligible however erfcx is approximated.
-__device__ __forceinline__ void trunc_terms2_far_f64(double t1, double t2, double& lnphi1,
-                                                     double& mills1, double& lnphi2,
-                                                     double& mills2, tab64_ptr tb)
-{
-    const double x1 = fmax(-0.5 * (t1 * t1), -760.0);
-    const double x2 = fmax(-0.5 * (t2 * t2), -760.0);
-    const double k1 = rint(x1 * kLog2e), k2 = rint(x2 * kLog2e);
-    double r1 = fma(k1, -kLn2Head, x1), r2 = fma(k2, -kLn2Head, x2);
-    r1 = fma(k1, -kLn2Tail, r1);
-    r2 = fma(k2, -kLn2Tail, r2);
-    double p1, p2;
-    horner2_tab<kExpN>(tb->exp, r1, r2, p1, p2);
-    const double e1 = ldexp(p1, (int)k1), e2 = ldexp(p2, (int)k2);
-    const double z1 = fmin(t1 * kInvSqrt2, kErfcxFarZmax64);
-    const double z2 = fmin(t2 * kInvSqrt2, kErfcxFarZmax64);
-    double P1, P2, Q1, Q2;
-    horner2_tab<kErfcxFarPN>(tb->erfcx_fp, z1, z2, P1, P2);
-    horner2_tab<kErfcxFarQN>(tb->erfcx_fq, z1, z2, Q1, Q2);
-    const double q1 = 0.5 * (e1 * P1) * rcp_f64(Q1);
-    const double q2 = 0.5 * (e2 * P2) * rcp_f64(Q2);
-    double L1, L2;
-    horner2_tab<kLog1pN>(tb->log1p, q1, q2, L1, L2);
-    lnphi1 = -q1 * L1;
-    lnphi2 = -q2 * L2;
-    double g1 = 1.0, g2 = 1.0;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        g1 = fma(g1, q1, 1.0);
-        g2 = fma(g2, q2, 1.0);
-    }
-    mills1 = kInvSqrt2Pi * e1 * g1;
-    mills2 = kInvSqrt2Pi * e2 * g2;
-}
-
 // The sweep's truncation terms.  Its sums need sum ln Phi(t) and m =
 // phi(t)/Phi(t) of each near pair (t below the sweep's skip point), and the
 // first only as a sum: it is -ln of the product of the pairs' 1/Phi, so a pair
 // costs one multiplication instead of a logarithm.  With e = exp(-t^2/2) and
 // 1 - Phi = e P/Q (fitted to an absolute error of 2^-53),
 //     1/Phi = Q / (Q - e P),   sigma m = (sigma/sqrt(2 pi)) e (1/Phi),
-// from one reciprocal.  Against the relative forms above (trunc_terms2_f64
-// and its far-range variant: 84 and 71 instructions a pair) this is 45, in
-// one form for every near t, with 26 coefficients instead of 44.
+// from one reciprocal.  Against the relative form above (84 instructions a
+// pair, 71 in a far-range variant) this is 45, in one form for every near t,
+// with 26 coefficients instead of 44.
 
 // what the near terms take from sigma, formed once per wave
 struct NearConst64 {
@@ -331,6 +245,53 @@ __device__ __forceinline__ void near_terms2_f64(double s2a, double s2b, double d
     gb = fma(qb, fma(vb, vb, vb), qb);
     ma = (ea * k.kappa) * ga;
     mb = (eb * k.kappa) * gb;
+}
+
+// -ln Phi(t) of two pairs in the same terms, 0 for a pair with near = false:
+// q = e P/Q, -ln Phi = 2 atanh(s) with s = q/(2 - q) = e P/(2Q - e P); c2 =
+// -log2(e) / (2 sigma^2) over s2 = delta^2
+__device__ __forceinline__ void neg_ln_phi2_f64(double s2a, double s2b, double ta, double tb2,
+                                                bool na, bool nb, double c2, tab64_ptr tb,
+                                                double& la, double& lb)
+{
+    constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
+    const double ha = fma(s2a, c2, kMagic), hb = fma(s2b, c2, kMagic);
+    const double fa = fma(s2a, c2, -(ha - kMagic)), fb = fma(s2b, c2, -(hb - kMagic));
+    double pa, pb;
+    horner2_tab<kExp2N - 1>(tb->exp2 + 1, fa, fb, pa, pb);
+    pa = fma(pa, fa, 1.0);
+    pb = fma(pb, fb, 1.0);
+    const double ea = na ? near_scale(pa, ha) : 0.0;
+    const double eb = nb ? near_scale(pb, hb) : 0.0;
+    const double za = fmin(ta, 10.0), zb = fmin(tb2, 10.0);
+    double Pa, Pb, Qa, Qb;
+    horner2_tab<kNearPN>(tb->near_p, za, zb, Pa, Pb);
+    horner2_tab<kNearQN - 1>(tb->near_q + 1, za, zb, Qa, Qb);
+    Qa = fma(Qa, za, 1.0);
+    Qb = fma(Qb, zb, 1.0);
+    const double xa = ea * Pa, xb = eb * Pb;
+    const double da = fma(2.0, Qa, -xa), db = fma(2.0, Qb, -xb);
+    const double ra = __builtin_amdgcn_rcp(da), rb = __builtin_amdgcn_rcp(db);
+    const double va = fma(-da, ra, 1.0), vb = fma(-db, rb, 1.0);
+    const double ua = xa * ra, ub = xb * rb;
+    const double sa = fma(ua, fma(va, va, va), ua), sb = fma(ub, fma(vb, vb, vb), ub);
+    double Aa, Ab;
+    horner2_tab<kAtanhN>(tb->atanh, sa * sa, sb * sb, Aa, Ab);
+    la = 2.0 * sa * Aa;
+    lb = 2.0 * sb * Ab;
+}
+
+// exp(x) for -700 <= x <= 0 (2^f and an exponent, as above), two at a time
+__device__ __forceinline__ void exp2_neg_f64(double x1, double x2, tab64_ptr tb, double& e1,
+                                             double& e2)
+{
+    constexpr double kMagic = 6755399441055744.0;
+    const double h1 = fma(x1, kLog2e, kMagic), h2 = fma(x2, kLog2e, kMagic);
+    const double f1 = fma(x1, kLog2e, -(h1 - kMagic)), f2 = fma(x2, kLog2e, -(h2 - kMagic));
+    double p1, p2;
+    horner2_tab<kExp2N - 1>(tb->exp2 + 1, f1, f2, p1, p2);
+    e1 = near_scale(fma(p1, f1, 1.0), h1);
+    e2 = near_scale(fma(p2, f2, 1.0), h2);
 }
 
 // ln g for a product g of up to 256 factors 1/Phi in [1, 2] (to rounding):
