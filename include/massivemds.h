@@ -56,7 +56,10 @@
  *     walks tile_rows/wr >= 8 rows); wc * wr <= 8 waves per work-group.  A
  *     plain count (wr = 0 in the second byte) means wr = 1.  One of
  *     tile_rows and 64*wc must divide the other.  The workspace depends on
- *     tile_rows and wc only, and must be sized with the same values.
+ *     tile_rows and wc only, and must be sized with the same values.  With
+ *     both 0, small FP64 problems (about a thousand locations) are evaluated
+ *     without tiles, whole gradient rows at a time: the same sums in another
+ *     order, so their last digits differ from those of a named tiling.
  */
 #ifndef MASSIVEMDS_H
 #define MASSIVEMDS_H

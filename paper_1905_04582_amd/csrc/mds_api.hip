@@ -297,6 +297,74 @@ FinalizeArgs finalize_args(const Tiling& t, const SweepArgs& s)
     return f;
 }
 
+// The small-problem form: FP64, the caller leaving the tiling to the library
+// (a caller that names one gets the tiled sweep, whose results a batch with
+// that tiling reproduces), at most kDirectMaxN locations, 32-bit element
+// offsets, and no per-wave trace asked for.
+// Beyond kDirectMaxN evaluating each pair twice costs more than the second
+// launch (D = 2, N = 1280: 11.2 us a step against 11.3, N = 1536: 13.2 against
+// 12.6; D = 6, N = 1536: 16.4 against 16.0).
+constexpr int64_t kDirectMaxN = 1280;
+
+// its scratch: a second position buffer (N x D doubles), then the parts of the
+// scalar sums (two doubles and a count per work-group)
+size_t direct_xbuf_bytes(int64_t n, int d) { return align_up((size_t)n * d * sizeof(double), 256); }
+size_t direct_bytes(int64_t n, int d)
+{
+    return direct_xbuf_bytes(n, d) +
+           (size_t)direct_blocks(n) * (2 * sizeof(double) + sizeof(uint32_t));
+}
+
+// (the scratch fits what the tiled sweep's partial sums would take, at least 24 N
+// D bytes; one location has no pair and may come without a Y)
+bool use_direct(int64_t n, int d, int y_dtype, int64_t ldx, int64_t ldy, int tile_rows,
+                int tile_waves, const WorkspaceLayout& lay)
+{
+    return y_dtype == MDS_F64 && tile_rows == 0 && tile_waves == 0 && n >= 2 &&
+           n <= kDirectMaxN && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
+           direct_bytes(n, d) <= lay.total && !g_tile_trace;
+}
+
+// the arguments every launch of it shares
+DirectArgs direct_args(void* ws, int64_t n, int d, const double* x, int64_t ldx, const void* y,
+                       int64_t ldy, const double* sigma, int truncated, double** xbuf)
+{
+    char* base = static_cast<char*>(ws);
+    const size_t xb = direct_xbuf_bytes(n, d);
+    const size_t sb = (size_t)direct_blocks(n) * 2 * sizeof(double);
+    *xbuf = reinterpret_cast<double*>(base);
+    DirectArgs a = {};
+    a.n = (int)n;
+    a.ldx = (int)ldx;
+    a.ldy = (int)ldy;
+    a.truncated = truncated;
+    a.x = x;
+    a.y = static_cast<const double*>(y);
+    a.sigma = sigma;
+    a.tscal = reinterpret_cast<double*>(base + xb);
+    a.tcount = reinterpret_cast<uint32_t*>(base + xb + sb);
+    return a;
+}
+
+// one launch and, with L or a derivative of sigma asked for, the sum of its parts
+hipError_t run_direct(int d, const DirectArgs& a, double* loglik, double* dsigma,
+                      double* dlogsigma, hipStream_t s)
+{
+    const bool scal = loglik || dsigma || dlogsigma;
+    hipError_t e = launch_direct(d, scal, a, s, g_ev_before, g_ev_after);
+    if (e != hipSuccess || !scal) return e;
+    FinalizeArgs f = {};
+    f.ntiles = direct_blocks(a.n);
+    f.tscal = a.tscal;
+    f.tcount = a.tcount;
+    f.sigma = a.sigma;
+    f.scale = a.scale;
+    f.loglik = loglik;
+    f.dsigma = dsigma;
+    f.dlogsigma = dlogsigma;
+    return launch_finalize(d, f, s);
+}
+
 // Scratch of mds_gradient_noalloc: the partial sums of one evaluation, in a
 // static device array (each device holds its own copy for the life of the
 // process).  Host code never uses the array's name as an address: its device
@@ -544,8 +612,18 @@ int mds_gradient(int64_t n, int32_t d, const double* x, int64_t ldx, const void*
     WorkspaceLayout lay;
     if ((st = check_workspace(t, d, workspace, workspace_bytes, &lay))) return st;
 
+    hipError_t e;
+    if (use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay)) {
+        double* xbuf;
+        DirectArgs da = direct_args(workspace, n, d, x, ldx, y, ldy, sigma_dev, trunc, &xbuf);
+        da.scale = scale_dev;
+        da.grad = grad;
+        da.ldg = ldg;
+        e = run_direct(d, da, loglik_dev, dsigma_dev, dlogsigma_dev, stream);
+        return e == hipSuccess ? MDS_OK : hip_fail(e, "gradient launch");
+    }
     SweepArgs sa = sweep_args(t, lay, workspace, n, x, ldx, y, ldy, sigma_dev, trunc);
-    hipError_t e = timed_sweep(y_dtype, d, true, t, sa, stream);
+    e = timed_sweep(y_dtype, d, true, t, sa, stream);
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
     FinalizeArgs fa = finalize_args(t, sa);
     fa.scale = scale_dev;
@@ -629,7 +707,36 @@ int mds_leapfrog(int64_t n, int32_t d, double* x, int64_t ldx, double* p, int64_
 
     // grad log pi and L at a point: sweep + finalize, optionally followed by
     // a kick of mult*eps and a drift of eps, fused into the finalize
-    auto evaluate = [&](double mult, int kick, int drift) -> int {
+    const bool direct = use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay);
+    double* xbuf = nullptr;  // direct: the positions alternate between x and this buffer
+    DirectArgs da = direct_args(workspace, n, d, x, ldx, y, ldy, sigma_dev, trunc, &xbuf);
+    da.prior = prior_dev;
+    da.grad = grad_io;
+    da.ldg = d;
+    da.ldp = ldp;
+    da.inv_mass = inv_mass;
+    da.step = step_dev;
+    // `need_loglik`: L is read after this evaluation (an energy, or the
+    // trajectory's end); `last`: the positions end in x
+    auto evaluate_direct = [&](double mult, int kick, int drift, bool need_loglik,
+                               bool last) -> int {
+        da.p = kick ? p : nullptr;
+        da.kick_mult = mult;
+        da.drift = drift;
+        double* to = drift ? (da.x == x ? xbuf : x) : (last && da.x != x ? x : nullptr);
+        da.x_out = to;
+        da.ldxo = to == x ? ldx : d;
+        const hipError_t err =
+            run_direct(d, da, need_loglik ? loglik_io : nullptr, nullptr, nullptr, stream);
+        if (err != hipSuccess) return hip_fail(err, "gradient launch");
+        if (drift) {
+            da.x = to;
+            da.ldx = (int)da.ldxo;
+        }
+        return MDS_OK;
+    };
+    auto evaluate = [&](double mult, int kick, int drift, bool need_loglik, bool last) -> int {
+        if (direct) return evaluate_direct(mult, kick, drift, need_loglik, last);
         hipError_t err = timed_sweep(y_dtype, d, true, t, sa, stream);
         if (err != hipSuccess) return hip_fail(err, "sweep launch");
         FinalizeArgs fa = finalize_args(t, sa);
@@ -653,7 +760,8 @@ int mds_leapfrog(int64_t n, int32_t d, double* x, int64_t ldx, double* p, int64_
     // first half kick (fused into the first evaluation when possible)
     const bool fuse_first = !cache_valid && !energy_start_dev && n_steps > 0;
     if (!cache_valid) {
-        if ((st = evaluate(0.5, fuse_first ? 1 : 0, fuse_first ? 1 : 0))) return st;
+        if ((st = evaluate(0.5, fuse_first ? 1 : 0, fuse_first ? 1 : 0, !fuse_first, false)))
+            return st;
     }
     if (energy_start_dev) {
         e = launch_energy(n, d, x, ldx, p, ldp, inv_mass, prior_dev, loglik_io, energy_start_dev,
@@ -666,7 +774,7 @@ int mds_leapfrog(int64_t n, int32_t d, double* x, int64_t ldx, double* p, int64_
     }
     for (int s = 1; s <= n_steps; ++s) {
         const bool last = (s == n_steps);
-        if ((st = evaluate(last ? 0.5 : 1.0, 1, last ? 0 : 1))) return st;
+        if ((st = evaluate(last ? 0.5 : 1.0, 1, last ? 0 : 1, last, last))) return st;
     }
     if (energy_end_dev) {
         e = launch_energy(n, d, x, ldx, p, ldp, inv_mass, prior_dev, loglik_io, energy_end_dev,

@@ -275,6 +275,35 @@ struct FinalizeArgs {
     int drift;
 };
 
+// The small-problem form (mds_direct.hip): rows per work-group
+constexpr int kDirectRows = 4;
+inline int direct_blocks(int64_t n) { return (int)((n + kDirectRows - 1) / kDirectRows); }
+
+// One launch of it: grad log pi at x (and, with the scalar sums, the
+// per-work-group parts of L and dL/dsigma), the kick of p and the drift.
+// Indices are 32-bit: n ldx and n ldy below 2^28.
+struct DirectArgs {
+    int n, ldx, ldy;
+    int truncated;
+    const double* x;
+    const double* y;
+    const double* sigma;
+    const double* scale;     // optional upstream scale
+    const double* prior;     // optional lambda: grad -= lambda x
+    double* grad;
+    int64_t ldg;
+    double* x_out;           // optional, not x: x after the drift (x itself without one)
+    int64_t ldxo;
+    double* p;               // optional: kicked by kick_mult eps grad
+    int64_t ldp;
+    const double* inv_mass;  // N x D contiguous (NULL = 1)
+    const double* step;      // eps
+    double kick_mult;
+    int drift;
+    double* tscal;           // direct_blocks(n) x 2 doubles
+    uint32_t* tcount;        // direct_blocks(n)
+};
+
 // One problem of a batch, as the persistent kernels see it (device table).
 struct BatchProblem {
     SweepArgs sweep;      // the problem's sweep arguments and partial buffers
@@ -302,6 +331,9 @@ struct BatchProblem {
 hipError_t launch_sweep(int y_dtype, int d, bool grad, const Tiling& t, const SweepArgs& a,
                         hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 hipError_t launch_finalize(int d, const FinalizeArgs& a, hipStream_t s);
+// scal: with the per-work-group sums of L and dL/dsigma
+hipError_t launch_direct(int d, bool scal, const DirectArgs& a, hipStream_t s,
+                         hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 hipError_t launch_batch_sweep(int y_dtype, bool grad, int maxd, const BatchProblem* probs,
                               int32_t count, int64_t total_tiles, unsigned long long* cursor,
                               int waves, size_t lds, int grid, hipStream_t s);

@@ -1,0 +1,74 @@
+"""The small-problem form of the FP64 evaluation (whole gradient rows per
+work-group) at the edges of its blocks of 4 rows and 16 columns and of its
+range: against the oracle, and its trajectories against those of the tiled
+sweep, which an explicit tiling selects.  Tolerances are those of the parity
+and trajectory tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1905_04582_amd import api
+from tests.test_gpu_parity import DEV, _rand, check64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 15, 16, 17, 64, 127, 129, 257, 1279, 1280, 1281])
+@pytest.mark.parametrize("d", [1, 2, 7, 8])
+def test_direct_evaluation(n, d):
+    x, y, mask, sigma = _rand(n, d, seed=31 * n + d)
+    ref = oracle.evaluate(x, y, sigma, mask)
+    # x and grad as parts of wider arrays; y with an odd leading dimension and
+    # an upper triangle that must not be read into the sums
+    yl = np.where(np.tril(np.ones((n, n)), -1) > 0, y, 7e3)
+    yb = torch.full((n, n + 3), 9e3, dtype=torch.float64, device=DEV)
+    yb[:, :n] = torch.as_tensor(yl)
+    if mask is not None:
+        yb[:, :n][torch.as_tensor(mask, device=DEV) != 0] = float("nan")
+    xb = torch.as_tensor(np.hstack([x, np.full((n, 2), np.nan)]), device=DEV)
+    gb = torch.full((n, d + 1), -5.0, dtype=torch.float64, device=DEV)
+    ws = api.alloc_workspace(api.mds_workspace_bytes(n, d, api.MDS_F64), DEV)
+    g, L, ds = api.mds_gradient(xb[:, :d], yb[:, :n], sigma, ws, grad=gb[:, :d])
+    L2 = api.mds_loglik(xb[:, :d], yb[:, :n], sigma, ws)
+    torch.cuda.synchronize()
+    got = dict(grad=g.cpu().numpy(), loglik=L.item(), dsigma=ds.item(), loglik_only=L2.item(),
+               m_obs=ref.m_obs)
+    check64(got, ref, f"n={n} d={d}")
+    assert torch.all(gb[:, d] == -5.0)
+
+
+@pytest.mark.parametrize("n,d", [(2, 2), (37, 3), (300, 2), (1001, 6)])
+@pytest.mark.parametrize("steps", [0, 1, 2, 5])
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("energies", [False, True])
+def test_direct_leapfrog(n, d, steps, cached, energies):
+    rng = np.random.default_rng(n + steps)
+    x0, y, mask, sigma = _rand(n, d, seed=n)
+    mom = rng.standard_normal((n, d))
+    im = torch.as_tensor(rng.uniform(0.5, 2.0, (n, d)), device=DEV)
+    out = []
+    for tile in ((0, 0), (8, 1)):
+        P = api.MDSProblem(y, d, mask, torch.float64, DEV, *tile)
+        # positions and momenta inside wider arrays
+        xb = torch.as_tensor(np.hstack([x0, np.full((n, 1), 3.0)]), device=DEV)
+        pb = torch.as_tensor(np.hstack([mom, np.full((n, 2), 4.0)]), device=DEV)
+        x, p = xb[:, :d], pb[:, :d]
+        g = torch.empty((n, d), dtype=torch.float64, device=DEV)
+        L = torch.empty((), dtype=torch.float64, device=DEV)
+        e = [torch.zeros((), dtype=torch.float64, device=DEV) for _ in range(2)]
+        kw = dict(inv_mass=im, prior=0.3)
+        if cached:
+            P.leapfrog(x, p, sigma, 1e-3, 0, g, L, **kw)
+        P.leapfrog(x, p, sigma, 1e-3, steps, g, L, cache_valid=cached,
+                   energy_start=e[0] if energies else None,
+                   energy_end=e[1] if energies else None, **kw)
+        torch.cuda.synchronize()
+        assert torch.all(xb[:, d] == 3.0) and torch.all(pb[:, d:] == 4.0)
+        out.append([t.cpu().numpy().copy() for t in (x, p, g, L, e[0], e[1])])
+    ev = oracle.evaluate(out[1][0], y, sigma, mask)
+    cond = max(float(np.max(ev.condrow)), 1e-300)
+    for k, (a, b) in enumerate(zip(*out)):
+        scale = {1: 1e-3 * (steps + 1) * cond + np.max(np.abs(b)), 2: cond + np.max(np.abs(b))}
+        tol = 1e-12 * scale.get(k, max(np.max(np.abs(b)), ev.abs_loglik if k >= 3 else 0.0))
+        assert np.max(np.abs(a - b)) <= tol, k
