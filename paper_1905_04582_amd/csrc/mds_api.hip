@@ -104,10 +104,24 @@ constexpr size_t kMaxSweepLds = 64 * 1024;
 // 4 waves keep every wave's walk short, so the last waves of the launch
 // finish soon after the others; larger problems run long enough for taller,
 // wider tiles, which write fewer partial sums.
-void default_tiling(int64_t n, int d, int dtype, int* br, int* wc, int* wr)
+//
+// With neither rows nor waves named (`whole`), problems of 1025 to 2048 locations
+// (1536 above D = 2), whose 8-row tiles of one wave outnumber the chip's 1024
+// SIMDs, take 32-row tiles over four row waves: waves as short, but a quarter of
+// the column-side partial sums for the finalize.  FP32 evaluations, D = 2 and 6:
+// N = 1280, 10.7 -> 8.5 and 13.9 -> 10.4 us; N = 1536, 11.8 -> 9.2 and 15.5 ->
+// 11.4; D = 2, N = 2000 against two row waves, 10.7 -> 10.3; D = 6 there, FP64,
+// they lose (20.3 -> 21.2 us a leapfrog step), as FP32 does at D = 5, N = 2048
+// (17.6 -> 17.8).  A caller that names one of the two gets the other as before,
+// so that every pair accepted stays so.
+void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, int* wr)
 {
     (void)dtype;
-    if (n <= 1536) {
+    if (whole && n > 1024 && n <= (d <= 2 ? 2048 : 1536)) {
+        *br = 32;
+        *wc = 1;
+        *wr = 4;
+    } else if (n <= 1536) {
         *br = 8;
         *wc = 1;
         *wr = 1;
@@ -151,7 +165,7 @@ int resolve_tiling(int64_t n, int d, int dtype, int tile_rows, int tile_waves, T
     }
     if (br == 0 || wc == 0) {
         int dbr, dwc, dwr;
-        default_tiling(n, d, dtype, &dbr, &dwc, &dwr);
+        default_tiling(n, d, dtype, br == 0 && wc == 0, &dbr, &dwc, &dwr);
         if (br == 0) br = dbr;
         if (wc == 0) {
             wc = dwc;
@@ -323,6 +337,17 @@ bool use_direct(int64_t n, int d, int y_dtype, int64_t ldx, int64_t ldy, int til
     return y_dtype == MDS_F64 && tile_rows == 0 && tile_waves == 0 && n >= 2 &&
            n <= kDirectMaxN && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
            direct_bytes(n, d) <= lay.total && !g_tile_trace;
+}
+
+// whether an output of n rows of d doubles may share memory with n rows of an
+// input (by the extent of both): the small-problem form reads every location and
+// its part of Y while it writes gradient rows
+bool rows_overlap(const double* out, int64_t ldo, int d, const void* in, int64_t ldi_bytes,
+                  int64_t row_bytes, int64_t n)
+{
+    const uintptr_t o0 = (uintptr_t)out, o1 = o0 + (uintptr_t)(((n - 1) * ldo + d) * 8);
+    const uintptr_t i0 = (uintptr_t)in, i1 = i0 + (uintptr_t)((n - 1) * ldi_bytes + row_bytes);
+    return o0 < i1 && i0 < o1;
 }
 
 // the arguments every launch of it shares
@@ -613,7 +638,9 @@ int mds_gradient(int64_t n, int32_t d, const double* x, int64_t ldx, const void*
     if ((st = check_workspace(t, d, workspace, workspace_bytes, &lay))) return st;
 
     hipError_t e;
-    if (use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay)) {
+    if (use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay) &&
+        !rows_overlap(grad, ldg, d, x, ldx * 8, d * 8, n) &&
+        !rows_overlap(grad, ldg, d, y, ldy * 8, n * 8, n)) {
         double* xbuf;
         DirectArgs da = direct_args(workspace, n, d, x, ldx, y, ldy, sigma_dev, trunc, &xbuf);
         da.scale = scale_dev;

@@ -72,3 +72,17 @@ def test_direct_leapfrog(n, d, steps, cached, energies):
         scale = {1: 1e-3 * (steps + 1) * cond + np.max(np.abs(b)), 2: cond + np.max(np.abs(b))}
         tol = 1e-12 * scale.get(k, max(np.max(np.abs(b)), ev.abs_loglik if k >= 3 else 0.0))
         assert np.max(np.abs(a - b)) <= tol, k
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gradient_over_its_input(shift):
+    # a gradient written over X (or over part of its rows' memory) is that of
+    # the X that was there: such a call takes the tiled sweep
+    x0, y, mask, sigma = _rand(300, 2, seed=77)
+    buf = torch.zeros(302, 2, dtype=torch.float64, device=DEV)
+    buf[:300] = torch.as_tensor(x0)
+    P = api.MDSProblem(y, 2, mask, torch.float64, DEV)
+    want, L0, _ = api.MDSProblem(y, 2, mask, torch.float64, DEV, 8, 1).gradient(buf[:300], sigma)
+    g, L, _ = P.gradient(buf[:300], sigma, grad=buf[shift:300 + shift])
+    torch.cuda.synchronize()
+    assert torch.equal(g, want) and torch.equal(L, L0)
