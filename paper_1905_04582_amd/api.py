@@ -164,8 +164,13 @@ def _check(status: int, where: str):
                                       f"{L.mds_last_error().decode()}")
 
 
+# The marshalling below runs on every call: at small N it, not the kernels, set
+# the pace (a gradient of 257 locations: 16.3 us, 5.6 of them the library's two
+# launches).  Pointers and streams are passed as plain integers, the current
+# stream is read as a raw handle (0.3 us; building torch's stream object took
+# 2.9), and shape and stride are read once per matrix (16.3 -> 12.6 us).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None, *tensors):
@@ -174,12 +179,12 @@ def _stream(stream=None, *tensors):
     converted inputs, device scalars made from numbers, fresh outputs) is
     recorded on it, so that the caching allocator does not hand its memory
     out again before the kernel has run."""
-    s = torch.cuda.current_stream() if stream is None else stream
-    if stream is not None:
-        for t in tensors:
-            if isinstance(t, torch.Tensor) and t.is_cuda:
-                t.record_stream(stream)
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    for t in tensors:
+        if isinstance(t, torch.Tensor) and t.is_cuda:
+            t.record_stream(stream)
+    return stream.cuda_stream
 
 
 def _ycode(y, truncated: bool) -> int:
@@ -202,13 +207,28 @@ def _dev_scalar(v, device):
     return torch.tensor(float(v), dtype=torch.float64, device=device)
 
 
+def _new_scalar(like, device):
+    """An uninitialised 0-d float64 tensor (a copy of a device scalar's form
+    costs a quarter less than naming one)."""
+    if like.dim() == 0 and like.device == device:
+        return torch.empty_like(like)
+    return torch.empty((), dtype=torch.float64, device=device)
+
+
 def _check_mat(t, name, dtype=torch.float64):
+    """(rows, columns, leading dimension) of a 2-D device tensor of `dtype` with
+    unit column stride (torch reports a stride of 0 for empty tensors)."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    if t.dim() != 2 or (t.numel() > 0 and t.shape[1] > 1 and t.stride(1) != 1):
+    if t.dim() != 2:
         raise ValueError(f"{name} must be 2-D with unit column stride")
+    r, c = t.shape
+    s0, s1 = t.stride()
+    if r > 0 and c > 1 and s1 != 1:
+        raise ValueError(f"{name} must be 2-D with unit column stride")
+    return r, c, (s0 if r > 1 else max(s0, c, 1))
 
 
 def _ld(t) -> int:
@@ -216,6 +236,16 @@ def _ld(t) -> int:
     if t.shape[0] <= 1:
         return max(int(t.stride(0)), int(t.shape[1]), 1)
     return int(t.stride(0))
+
+
+def _mask_bytes(mask, device):
+    """A mask (non-zero = set) as contiguous bytes on `device`; byte and boolean
+    masks are passed as they are (the kernels test for non-zero)."""
+    m = torch.as_tensor(mask)
+    if m.dtype not in (torch.uint8, torch.bool):
+        m = m != 0
+    m = m.to(device=device).contiguous()
+    return m if m.dtype == torch.uint8 else m.view(torch.uint8)
 
 
 def version() -> int:
@@ -280,7 +310,7 @@ def mds_prepare_y(y_src: torch.Tensor, out_dtype: torch.dtype = torch.float64, m
     buf = torch.empty((max(n, 1), ldy), dtype=out_dtype, device=y_src.device)
     if mask is not None:
         _check_mat(mask, "mask", torch.uint8)
-    m_obs = torch.zeros((), dtype=torch.int64, device=y_src.device) if count else None
+    m_obs = torch.empty((), dtype=torch.int64, device=y_src.device) if count else None
     _check(lib().mds_prepare_y(_ptr(y_src), _dtype_code(y_src.dtype), _ld(y_src),
                                _ptr(mask), _ld(mask) if mask is not None else 0,
                                _ptr(buf), _dtype_code(out_dtype), ldy, n, _ptr(perm),
@@ -345,13 +375,12 @@ def mds_permute_rows(src: torch.Tensor, perm: torch.Tensor, inverse: bool = Fals
 
 def mds_loglik(x, y, sigma, workspace, out=None, tile_rows=0, tile_waves=0, stream=None,
                truncated=True):
-    _check_mat(x, "x")
-    _check_mat(y, "y", y.dtype)
-    n, d = x.shape
+    n, d, ldx = _check_mat(x, "x")
+    _, _, ldy = _check_mat(y, "y", y.dtype)
     sig = _dev_scalar(sigma, x.device)
-    out = torch.empty((), dtype=torch.float64, device=x.device) if out is None else out
-    _check(lib().mds_loglik(n, d, _ptr(x), _ld(x), _ptr(y), _ycode(y, truncated),
-                            _ld(y), _ptr(sig), _ptr(out), _ptr(workspace),
+    out = _new_scalar(sig, x.device) if out is None else out
+    _check(lib().mds_loglik(n, d, _ptr(x), ldx, _ptr(y), _ycode(y, truncated),
+                            ldy, _ptr(sig), _ptr(out), _ptr(workspace),
                             workspace.numel(), tile_rows, tile_waves,
                             _stream(stream, x, y, sig, out, workspace)),
            "mds_loglik")
@@ -363,20 +392,19 @@ def mds_gradient(x, y, sigma, workspace, scale=None, grad=None, loglik=None, dsi
                  stream=None, truncated=True):
     """Returns (grad N x D, loglik scalar or None, dsigma scalar or None); an
     optional `dlogsigma` device scalar receives scale * sigma * dL/dsigma."""
-    _check_mat(x, "x")
-    _check_mat(y, "y", y.dtype)
-    n, d = x.shape
+    n, d, ldx = _check_mat(x, "x")
+    _, _, ldy = _check_mat(y, "y", y.dtype)
     dev = x.device
     sig = _dev_scalar(sigma, dev)
     sc = None if scale is None else _dev_scalar(scale, dev)
     grad = torch.empty((n, d), dtype=torch.float64, device=dev) if grad is None else grad
-    _check_mat(grad, "grad")
+    _, _, ldg = _check_mat(grad, "grad")
     if want_loglik and loglik is None:
-        loglik = torch.empty((), dtype=torch.float64, device=dev)
+        loglik = _new_scalar(sig, dev)
     if want_dsigma and dsigma is None:
-        dsigma = torch.empty((), dtype=torch.float64, device=dev)
-    _check(lib().mds_gradient(n, d, _ptr(x), _ld(x), _ptr(y), _ycode(y, truncated),
-                              _ld(y), _ptr(sig), _ptr(sc), _ptr(grad), _ld(grad),
+        dsigma = _new_scalar(sig, dev)
+    _check(lib().mds_gradient(n, d, _ptr(x), ldx, _ptr(y), _ycode(y, truncated),
+                              ldy, _ptr(sig), _ptr(sc), _ptr(grad), ldg,
                               _ptr(loglik), _ptr(dsigma), _ptr(dlogsigma), _ptr(workspace),
                               workspace.numel(), tile_rows, tile_waves,
                               _stream(stream, x, y, sig, sc, grad, loglik, dsigma, dlogsigma,
@@ -563,7 +591,7 @@ class MDSProblem:
                    torch.float32).contiguous()
         m = None
         if mask is not None:
-            m = (torch.as_tensor(mask) != 0).to(device=device, dtype=torch.uint8).contiguous()
+            m = _mask_bytes(mask, device)
         self.n, self.d, self.dtype, self.device = n, int(d), dtype, torch.device(device)
         self.truncated = bool(truncated)
         self.perm = None
@@ -669,7 +697,7 @@ class MDSBatch:
                        else torch.float32).contiguous()
             m = pr.get("mask")
             if m is not None:
-                m = (torch.as_tensor(m) != 0).to(device=self.device, dtype=torch.uint8).contiguous()
+                m = _mask_bytes(m, self.device)
             perm = None
             if pr.get("order") is not None:
                 xo = torch.as_tensor(pr["order"]).to(device=self.device,
@@ -811,10 +839,10 @@ class HeldOutPairs:
         y = torch.as_tensor(y)
         src = y.to(device=dev, dtype=torch.float64 if y.dtype == torch.float64 else
                    torch.float32).contiguous()
-        h = (torch.as_tensor(heldout) != 0).to(device=dev, dtype=torch.uint8).contiguous()
+        h = _mask_bytes(heldout, dev)
         m = None
         if mask is not None:
-            m = (torch.as_tensor(mask) != 0).to(device=dev, dtype=torch.uint8).contiguous()
+            m = _mask_bytes(mask, dev)
         n = src.shape[0]
         if src.dim() != 2 or src.shape[1] != n or h.shape != src.shape or \
                 (m is not None and m.shape != src.shape):
@@ -822,7 +850,7 @@ class HeldOutPairs:
         nb = ctypes.c_size_t()
         _check(lib().mds_heldout_workspace_bytes(n, ctypes.byref(nb)), "mds_heldout_workspace_bytes")
         ws = alloc_workspace(nb.value, dev)
-        cnt = torch.zeros((), dtype=torch.int64, device=dev)
+        cnt = torch.empty((), dtype=torch.int64, device=dev)
         args = (_ptr(src), _dtype_code(src.dtype), _ld(src), _ptr(m), _ld(m) if m is not None else 0,
                 _ptr(h), _ld(h), n)
         _check(lib().mds_heldout_count(*args, _ptr(cnt), _ptr(ws), ws.numel(),

@@ -90,3 +90,30 @@ def test_heldout_rows_of_any_alignment(n, pad, off, masked):
     assert np.array_equal(pi.cpu().numpy()[:len(i)], i)
     assert np.array_equal(pj.cpu().numpy()[:len(i)], j)
     assert np.array_equal(py.cpu().numpy()[:len(i)], yn[i, j])
+
+
+@pytest.mark.parametrize("kind", ["uint8", "bool", "int32", "float64", "strided", "numpy"])
+def test_masks_of_any_type(kind):
+    # any type marks its non-zero entries; the caller's mask is left alone
+    rng = np.random.default_rng(3)
+    n = 70
+    y = rng.random((n, n))
+    m = np.tril(rng.random((n, n)) < 0.3, -1)
+    m = m | m.T
+    if kind == "numpy":
+        mask = m
+    elif kind == "strided":
+        wide = torch.zeros((n, 2 * n), dtype=torch.bool, device=DEV)
+        wide[:, ::2] = torch.as_tensor(m)
+        mask = wide[:, ::2]
+    else:
+        mask = torch.as_tensor(m).to(getattr(torch, kind)).to(DEV) * (7 if kind == "uint8" else 1)
+    before = mask.copy() if kind == "numpy" else mask.clone()
+    P = api.MDSProblem(y, 2, mask)
+    H = api.HeldOutPairs(y, mask)
+    want = np.where(m, np.nan, y)
+    assert np.array_equal(P.y[:, :n].cpu().numpy(), want, equal_nan=True)
+    assert int(P.m_obs.item()) == int((~m).sum() - n) // 2
+    assert H.m == int(np.tril(m, -1).sum())
+    assert np.array_equal(np.asarray(before if kind == "numpy" else before.cpu()),
+                          np.asarray(mask if kind == "numpy" else mask.cpu()))
