@@ -436,7 +436,8 @@ typedef struct mds_batch_plan {
     int32_t tile_waves;      /* waves per work-group of the persistent sweep (wc * wr) */
     int32_t grid;            /* persistent work-groups */
     int32_t max_d;           /* largest D of the batch */
-    int32_t flags;           /* bit 0: every problem has momenta, step, grad and loglik */
+    int32_t flags;           /* bit 0: every problem has momenta, step, grad and loglik;
+                                bit 1: the sweep's form for more tiles than are resident */
     int64_t total_tiles;
     int64_t elem_blocks;
     size_t lds_bytes;

@@ -334,10 +334,11 @@ hipError_t launch_finalize(int d, const FinalizeArgs& a, hipStream_t s);
 // scal: with the per-work-group sums of L and dL/dsigma
 hipError_t launch_direct(int d, bool scal, const DirectArgs& a, hipStream_t s,
                          hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-hipError_t launch_batch_sweep(int y_dtype, bool grad, int maxd, const BatchProblem* probs,
+// lean: the form with fewer registers (FP64 has only this one)
+hipError_t launch_batch_sweep(int y_dtype, bool grad, int maxd, bool lean, const BatchProblem* probs,
                               int32_t count, int64_t total_tiles, unsigned long long* cursor,
                               int waves, size_t lds, int grid, hipStream_t s);
-int batch_sweep_blocks_per_cu(int y_dtype, bool grad, int maxd, int waves, size_t lds);
+int batch_sweep_blocks_per_cu(int y_dtype, int maxd, bool lean, int waves, size_t lds);
 // kick_mult / kick / drift: the leapfrog update fused into the finalize
 // (p += kick_mult eps g when kick, then x += eps p when drift); 0, 0, 0 for
 // a plain evaluation

@@ -15,14 +15,14 @@ hipError_t launch_sweep_f64(int d, bool grad, const Tiling& t, const SweepArgs& 
 hipError_t launch_sweep_f32(int d, bool grad, const Tiling& t, const SweepArgs& a, hipStream_t s,
                             hipEvent_t start, hipEvent_t stop);
 
-hipError_t launch_batch_sweep_f64(bool grad, int maxd, const BatchProblem* probs, int32_t count,
+hipError_t launch_batch_sweep_f64(bool grad, int maxd, bool lean, const BatchProblem* probs, int32_t count,
                                  int64_t total_tiles, unsigned long long* cursor, int waves,
                                  size_t lds, int grid, hipStream_t s);
-hipError_t launch_batch_sweep_f32(bool grad, int maxd, const BatchProblem* probs, int32_t count,
+hipError_t launch_batch_sweep_f32(bool grad, int maxd, bool lean, const BatchProblem* probs, int32_t count,
                                  int64_t total_tiles, unsigned long long* cursor, int waves,
                                  size_t lds, int grid, hipStream_t s);
-int batch_sweep_blocks_per_cu_f64(bool grad, int maxd, int waves, size_t lds);
-int batch_sweep_blocks_per_cu_f32(bool grad, int maxd, int waves, size_t lds);
+int batch_sweep_blocks_per_cu_f64(int maxd, bool lean, int waves, size_t lds);
+int batch_sweep_blocks_per_cu_f32(int maxd, bool lean, int waves, size_t lds);
 
 hipError_t launch_sweep(int y_dtype, int d, bool grad, const Tiling& t, const SweepArgs& a,
                         hipStream_t s, hipEvent_t start, hipEvent_t stop)
@@ -31,20 +31,20 @@ hipError_t launch_sweep(int y_dtype, int d, bool grad, const Tiling& t, const Sw
                         : launch_sweep_f32(d, grad, t, a, s, start, stop);
 }
 
-hipError_t launch_batch_sweep(int y_dtype, bool grad, int maxd, const BatchProblem* probs,
+hipError_t launch_batch_sweep(int y_dtype, bool grad, int maxd, bool lean, const BatchProblem* probs,
                               int32_t count, int64_t total_tiles, unsigned long long* cursor,
                               int waves, size_t lds, int grid, hipStream_t s)
 {
-    return y_dtype == 0 ? launch_batch_sweep_f64(grad, maxd, probs, count, total_tiles, cursor,
+    return y_dtype == 0 ? launch_batch_sweep_f64(grad, maxd, lean, probs, count, total_tiles, cursor,
                                                  waves, lds, grid, s)
-                        : launch_batch_sweep_f32(grad, maxd, probs, count, total_tiles, cursor,
+                        : launch_batch_sweep_f32(grad, maxd, lean, probs, count, total_tiles, cursor,
                                                  waves, lds, grid, s);
 }
 
-int batch_sweep_blocks_per_cu(int y_dtype, bool grad, int maxd, int waves, size_t lds)
+int batch_sweep_blocks_per_cu(int y_dtype, int maxd, bool lean, int waves, size_t lds)
 {
-    return y_dtype == 0 ? batch_sweep_blocks_per_cu_f64(grad, maxd, waves, lds)
-                        : batch_sweep_blocks_per_cu_f32(grad, maxd, waves, lds);
+    return y_dtype == 0 ? batch_sweep_blocks_per_cu_f64(maxd, lean, waves, lds)
+                        : batch_sweep_blocks_per_cu_f32(maxd, lean, waves, lds);
 }
 
 // Finalize: one work-group per 64 consecutive gradient elements e = (k, d),

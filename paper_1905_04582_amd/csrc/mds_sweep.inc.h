@@ -123,14 +123,16 @@ __host__ __device__ constexpr int reduce_group(int outputs)
 }
 
 // One tile of one problem, processed by the whole work-group; `lds` is the
-// work-group's dynamic LDS (sweep_lds_bytes).  Ends with a barrier, so the
-// caller may reuse the LDS for the next tile straight away.
+// work-group's dynamic LDS (sweep_lds_bytes), `tid` the thread's index in the
+// work-group.  Ends with a barrier, so the caller may reuse the LDS for the
+// next tile straight away.
 template <typename T, int D, bool GRAD>
-__device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t tile, double* lds)
+__device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t tile, double* lds,
+                                           const int tid)
 {
     constexpr int RB = sweep_stage_rows(D);
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = tid & (kWave - 1);
+    const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int waves = blockDim.x / kWave;
     const int br = a.br, cw = a.cw, wc = a.wc;
     const int wu = w & (wc - 1);  // this wave's column group (wc is a power of two)
@@ -505,13 +507,13 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
         // tile row sums: the column groups' copies added in order
         double* rp = a.rowpart + (size_t)tile * br * D;
         const int nrow = (int)(row1 - row0) * D;
-        for (int k = threadIdx.x; k < nrow; k += blockDim.x) {
+        for (int k = tid; k < nrow; k += blockDim.x) {
             double s = 0.0;
             for (int u = 0; u < wc; ++u) s += lds[(size_t)u * br * D + k];
             rp[k] = s;
         }
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double sr = 0.0, ss = 0.0, sc = 0.0;
         for (int ww = 0; ww < waves; ++ww) {
             sr += lscal[ww * 4 + 0];
@@ -547,7 +549,7 @@ __global__ void __launch_bounds__(512)
     const bool traced = a.trace != nullptr;
     unsigned long long t0 = 0;
     if (traced) t0 = __builtin_amdgcn_s_memrealtime();
-    sweep_tile<T, D, GRAD>(a, blockIdx.x, lds);
+    sweep_tile<T, D, GRAD>(a, blockIdx.x, lds, threadIdx.x);
     if (traced) {
         // diagnostics: start and end clock (100 MHz) and HW_ID of each wave
         const unsigned long long t1 = __builtin_amdgcn_s_memrealtime();
@@ -567,7 +569,20 @@ __global__ void __launch_bounds__(512)
 // a tile is processed never changes what it writes, so the results are those
 // of the single-problem sweep, bit for bit.  MAXD bounds the D cases compiled
 // in, so the register allocation follows the largest D of the batch.
-template <typename T, bool GRAD, int MAXD>
+//
+// Bound by VALU issue, as the single sweep, at the waves that the registers
+// leave.  What every compiled D derives from the thread index (column, row
+// and LDS addresses) is loop-invariant, and the compiler computes it ahead of
+// the tile loop and holds it for all D at once.  The LEAN form hides the index
+// from it, so that each tile derives its own: MAXD = 6 goes from 159 to 121
+// registers in FP32 (three to four waves per SIMD) and from 197 to 163 in FP64
+// (two to three); 32 problems of 500 to 8000 locations take 698 -> 651 us in
+// FP32 and 1429 -> 1262 us in FP64, and 12 to 32 of up to 2000 in FP64 154 ->
+// 129.  In FP32 the ordinary form stays for a batch whose tiles are all
+// resident at once: three waves per SIMD is then what its two-wave
+// work-groups fill evenly, where four let some SIMDs hold four and others two
+// (held to three, the lean form measures the same).
+template <typename T, bool GRAD, int MAXD, bool LEAN>
 __global__ void __launch_bounds__(512)
     __attribute__((amdgpu_waves_per_eu(batch_sweep_waves_per_simd<T, MAXD>()))) batch_sweep_kernel(const BatchProblem* __restrict__ probs,
                                                           int32_t count, int64_t total_tiles,
@@ -578,7 +593,9 @@ __global__ void __launch_bounds__(512)
     for (;;) {
         if (threadIdx.x == 0) next = (int64_t)atomicAdd(cursor, 1ull);
         __syncthreads();
-        const int64_t g = next;
+        // (uniform: the problem's table entry then comes through scalar loads
+        // and its fields stay in scalar registers)
+        const int64_t g = read_first_lane(next);
         __syncthreads();
         if (g >= total_tiles) break;
         int lo = 0, hi = count - 1;
@@ -591,79 +608,94 @@ __global__ void __launch_bounds__(512)
         }
         const BatchProblem& P = probs[lo];
         const SweepArgs a = P.sweep;
+        int tid = threadIdx.x;
+        if constexpr (LEAN) asm volatile("" : "+v"(tid));
         const int64_t tile = g - P.tile_base;
         switch (P.d) {
-            case 1: sweep_tile<T, 1, GRAD>(a, tile, lds); break;
-            case 2: sweep_tile<T, 2, GRAD>(a, tile, lds); break;
-            case 3: if constexpr (MAXD >= 3) sweep_tile<T, 3, GRAD>(a, tile, lds); break;
-            case 4: if constexpr (MAXD >= 4) sweep_tile<T, 4, GRAD>(a, tile, lds); break;
-            case 5: if constexpr (MAXD >= 5) sweep_tile<T, 5, GRAD>(a, tile, lds); break;
-            case 6: if constexpr (MAXD >= 6) sweep_tile<T, 6, GRAD>(a, tile, lds); break;
-            case 7: if constexpr (MAXD >= 7) sweep_tile<T, 7, GRAD>(a, tile, lds); break;
-            default: if constexpr (MAXD >= 8) sweep_tile<T, 8, GRAD>(a, tile, lds); break;
+            case 1: sweep_tile<T, 1, GRAD>(a, tile, lds, tid); break;
+            case 2: sweep_tile<T, 2, GRAD>(a, tile, lds, tid); break;
+            case 3: if constexpr (MAXD >= 3) sweep_tile<T, 3, GRAD>(a, tile, lds, tid); break;
+            case 4: if constexpr (MAXD >= 4) sweep_tile<T, 4, GRAD>(a, tile, lds, tid); break;
+            case 5: if constexpr (MAXD >= 5) sweep_tile<T, 5, GRAD>(a, tile, lds, tid); break;
+            case 6: if constexpr (MAXD >= 6) sweep_tile<T, 6, GRAD>(a, tile, lds, tid); break;
+            case 7: if constexpr (MAXD >= 7) sweep_tile<T, 7, GRAD>(a, tile, lds, tid); break;
+            default: if constexpr (MAXD >= 8) sweep_tile<T, 8, GRAD>(a, tile, lds, tid); break;
         }
     }
+}
+
+// FP64 has only the lean form.
+template <typename T, bool GRAD, int MAXD>
+hipError_t launch_batch_sweep_m(bool lean, const BatchProblem* probs, int32_t count,
+                                int64_t total_tiles, unsigned long long* cursor, dim3 g, dim3 b,
+                                size_t lds, hipStream_t s)
+{
+    if constexpr (sizeof(T) == 4)
+        if (!lean) {
+            hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, MAXD, false>), g, b, lds, s, probs,
+                               count, total_tiles, cursor);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, MAXD, true>), g, b, lds, s, probs, count,
+                       total_tiles, cursor);
+    return hipGetLastError();
 }
 
 // smallest compiled bound that covers max_d
 inline int batch_maxd_bucket(int max_d) { return max_d <= 2 ? 2 : (max_d <= 4 ? 4 : (max_d <= 6 ? 6 : 8)); }
 
 template <typename T, bool GRAD>
-hipError_t launch_batch_sweep_g(int maxd, const BatchProblem* probs, int32_t count,
+hipError_t launch_batch_sweep_g(int maxd, bool lean, const BatchProblem* probs, int32_t count,
                                 int64_t total_tiles, unsigned long long* cursor, dim3 g, dim3 b,
                                 size_t lds, hipStream_t s)
 {
+#define MDS_BATCH_LAUNCH(M) \
+    return launch_batch_sweep_m<T, GRAD, M>(lean, probs, count, total_tiles, cursor, g, b, lds, s)
     switch (batch_maxd_bucket(maxd)) {
-        case 2:
-            hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, 2>), g, b, lds, s, probs, count,
-                               total_tiles, cursor);
-            break;
-        case 4:
-            hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, 4>), g, b, lds, s, probs, count,
-                               total_tiles, cursor);
-            break;
-        case 6:
-            hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, 6>), g, b, lds, s, probs, count,
-                               total_tiles, cursor);
-            break;
-        default:
-            hipLaunchKernelGGL((batch_sweep_kernel<T, GRAD, 8>), g, b, lds, s, probs, count,
-                               total_tiles, cursor);
-            break;
+        case 2: MDS_BATCH_LAUNCH(2);
+        case 4: MDS_BATCH_LAUNCH(4);
+        case 6: MDS_BATCH_LAUNCH(6);
+        default: MDS_BATCH_LAUNCH(8);
     }
-    return hipGetLastError();
+#undef MDS_BATCH_LAUNCH
 }
 
 template <typename T>
-hipError_t launch_batch_sweep_t(bool grad, int maxd, const BatchProblem* probs, int32_t count,
-                                int64_t total_tiles, unsigned long long* cursor, int waves,
-                                size_t lds, int grid, hipStream_t s)
+hipError_t launch_batch_sweep_t(bool grad, int maxd, bool lean, const BatchProblem* probs,
+                                int32_t count, int64_t total_tiles, unsigned long long* cursor,
+                                int waves, size_t lds, int grid, hipStream_t s)
 {
     if (total_tiles == 0) return hipSuccess;
     const dim3 g((unsigned)grid), b((unsigned)(waves * kWave));
-    return grad ? launch_batch_sweep_g<T, true>(maxd, probs, count, total_tiles, cursor, g, b,
-                                                lds, s)
-                : launch_batch_sweep_g<T, false>(maxd, probs, count, total_tiles, cursor, g, b,
-                                                 lds, s);
+    return grad ? launch_batch_sweep_g<T, true>(maxd, lean, probs, count, total_tiles, cursor, g,
+                                                b, lds, s)
+                : launch_batch_sweep_g<T, false>(maxd, lean, probs, count, total_tiles, cursor, g,
+                                                 b, lds, s);
 }
 
-template <typename T, bool GRAD, int MAXD>
-int occupancy_of(int waves, size_t lds)
+template <typename T, int MAXD>
+int occupancy_of(bool lean, int waves, size_t lds)
 {
     int nb = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &nb, batch_sweep_kernel<T, GRAD, MAXD>, waves * kWave, lds);
+    hipError_t e;
+    if (sizeof(T) == 8 || lean)
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, batch_sweep_kernel<T, true, MAXD, true>, waves * kWave, lds);
+    else
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &nb, batch_sweep_kernel<T, true, MAXD, sizeof(T) == 8>, waves * kWave, lds);
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
+// resident work-groups per CU of the gradient form
 template <typename T>
-int batch_sweep_blocks_per_cu(bool grad, int maxd, int waves, size_t lds)
+int batch_sweep_blocks_per_cu(int maxd, bool lean, int waves, size_t lds)
 {
     switch (batch_maxd_bucket(maxd)) {
-        case 2: return grad ? occupancy_of<T, true, 2>(waves, lds) : occupancy_of<T, false, 2>(waves, lds);
-        case 4: return grad ? occupancy_of<T, true, 4>(waves, lds) : occupancy_of<T, false, 4>(waves, lds);
-        case 6: return grad ? occupancy_of<T, true, 6>(waves, lds) : occupancy_of<T, false, 6>(waves, lds);
-        default: return grad ? occupancy_of<T, true, 8>(waves, lds) : occupancy_of<T, false, 8>(waves, lds);
+        case 2: return occupancy_of<T, 2>(lean, waves, lds);
+        case 4: return occupancy_of<T, 4>(lean, waves, lds);
+        case 6: return occupancy_of<T, 6>(lean, waves, lds);
+        default: return occupancy_of<T, 8>(lean, waves, lds);
     }
 }
 

@@ -52,6 +52,14 @@ __device__ __forceinline__ T group_sum(T v)
     return v;
 }
 
+// a value that every lane holds, as a scalar
+__device__ __forceinline__ int64_t read_first_lane(int64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
 __device__ __forceinline__ int read_lane63(int v) { return __builtin_amdgcn_readlane(v, 63); }
 __device__ __forceinline__ double read_lane63(double v)
 {
