@@ -133,15 +133,15 @@ __device__ __forceinline__ double rcp_f64(double d)
 
 // 1/sqrt(x) for finite x >= DBL_MIN: hardware estimate r (relative error
 // below 2^-24 on gfx950), then one correction of third order: with
-// e = (1 - x r^2)/2, 1/sqrt(x) = r (1 + e + 3/2 e^2 + 5/2 e^3 + ...), and
+// e = 1 - x r^2, 1/sqrt(x) = r (1 + e/2 + 3/8 e^2 + 5/16 e^3 + ...), and
 // the first omitted term is below 2^-70 of the result, so the final fma's
 // rounding sets the error (a Newton step only squares it: two would be
-// needed)
+// needed).  Five operations after the estimate.
 __device__ __forceinline__ double rsqrt_f64(double x)
 {
     const double r = __builtin_amdgcn_rsq(x);
-    const double e = fma(-0.5 * x, r * r, 0.5);
-    return fma(r * e, fma(1.5, e, 1.0), r);
+    const double e = fma(-(x * r), r, 1.0);
+    return fma(r, e * fma(0.375, e, 0.5), r);
 }
 
 constexpr int kExpN = sizeof(kExpC64) / sizeof(double);

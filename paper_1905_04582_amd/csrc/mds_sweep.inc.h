@@ -341,6 +341,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
             const T rb = okb ? fma(s2b, rsb, -yb) : T(0);
             bA = fma(ra, ra, bA);
             bA = fma(rb, rb, bA);
+            // (FP64: summed here, before the branch below, so that the
+            // residuals' registers become the weights' without a copy)
+            if constexpr (sizeof(T) == 8) asm volatile("" : "+v"(bA));
             // sigma^2 w (x_i - x_j)/delta = (delta - y + m sigma) (x_i -
             // x_j)/delta, m = 0 past the skip point
             T ca, cb;
