@@ -1260,13 +1260,15 @@ int mds_batch_init(const mds_problem_desc* descs, int32_t count, int32_t y_dtype
     if ((st = device_cu_count(&cus))) return st;
     int max_d = 1;
     for (int32_t k = 0; k < count; ++k) max_d = descs[k].d > max_d ? descs[k].d : max_d;
-    // FP32: the ordinary form where all tiles are resident at once, else the
-    // lean one with its higher residency (batch_sweep_kernel).  FP32, D up to
-    // 6, ordinary against lean: 1524 tiles 94.3 : 102.1 us, 1310 tiles
-    // 90.7 : 97.2; 2101 tiles 117.3 : 108.0, 21307 tiles 699 : 651.
+    // FP32: the lean form where the tiles outnumber the work-groups that are
+    // resident with it (batch_sweep_kernel), else the ordinary one.  D up to 6,
+    // 1536 and 2048 work-groups resident, ordinary against lean: 2395 tiles
+    // 124.6 : 124.9 us, 2101 tiles 117.3 : 108.0, 21307 tiles 699 : 651; between
+    // the two numbers either may win (1708 tiles 100 : 96, 1811 tiles 101 : 108,
+    // 1940 tiles 105 : 109); 1310 and 1524 tiles 90.7 : 97.2 and 94.3 : 102.1.
     const bool lean =
         y_dtype == MDS_F64 ||
-        tiles > (int64_t)cus * batch_sweep_blocks_per_cu(y_dtype, max_d, false, waves, max_lds);
+        tiles > (int64_t)cus * batch_sweep_blocks_per_cu(y_dtype, max_d, true, waves, max_lds);
     // no more work-groups than tiles (rounded up to whole CUs): one that finds
     // the cursor exhausted still takes a slot and its share of the atomics.
     // 64 tiles (32 problems of 60 to 200 locations, FP32): 62 -> 47 us.

@@ -597,8 +597,8 @@ __global__ void __launch_bounds__(512)
 // registers in FP32 (three to four waves per SIMD) and from 197 to 163 in FP64
 // (two to three); 32 problems of 500 to 8000 locations take 698 -> 651 us in
 // FP32 and 1429 -> 1262 us in FP64, and 12 to 32 of up to 2000 in FP64 154 ->
-// 129.  In FP32 the ordinary form stays for a batch whose tiles are all
-// resident at once: three waves per SIMD is then what its two-wave
+// 129.  In FP32 the ordinary form stays for a batch of about as many tiles as
+// are resident at once, or fewer: three waves per SIMD is then what its two-wave
 // work-groups fill evenly, where four let some SIMDs hold four and others two
 // (held to three, the lean form measures the same).
 template <typename T, bool GRAD, int MAXD, bool LEAN>
