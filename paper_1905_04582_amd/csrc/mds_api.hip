@@ -105,23 +105,45 @@ constexpr size_t kMaxSweepLds = 64 * 1024;
 // finish soon after the others; larger problems run long enough for taller,
 // wider tiles, which write fewer partial sums.
 //
-// With neither rows nor waves named (`whole`), problems of 1025 to 2048 locations
-// (1536 above D = 2), whose 8-row tiles of one wave outnumber the chip's 1024
-// SIMDs, take 32-row tiles over four row waves: waves as short, but a quarter of
-// the column-side partial sums for the finalize.  FP32 evaluations, D = 2 and 6:
-// N = 1280, 10.7 -> 8.5 and 13.9 -> 10.4 us; N = 1536, 11.8 -> 9.2 and 15.5 ->
-// 11.4; D = 2, N = 2000 against two row waves, 10.7 -> 10.3; D = 6 there, FP64,
-// they lose (20.3 -> 21.2 us a leapfrog step), as FP32 does at D = 5, N = 2048
-// (17.6 -> 17.8).  A caller that names one of the two gets the other as before,
-// so that every pair accepted stays so.
+// With neither rows nor waves named (`whole`), the tiles below come first.  They
+// trade the same two things where four waves share a tile: fewer partial sums
+// for the finalize against longer walks (one evaluation, both orders, earlier
+// shape -> this one).  A caller that names rows or waves gets the other as
+// before, so that every pair accepted stays so.
+//   1025..2048 (D <= 4; 1536 above), 32 rows over four waves: their 8-row tiles
+//     of one wave outnumber the chip's 1024 SIMDs.  FP32, N = 1280, D = 2 and 6,
+//     10.7 -> 8.5 and 13.9 -> 10.4 us; FP64, N = 1600, D = 3, 14.0 -> 12.3;
+//     above the line D = 6, FP64, loses (20.3 -> 21.2 us a leapfrog step).
+//   2049..3072 (FP32, or D > 2), 64 rows over four waves: N = 2300, D = 3,
+//     14.6 -> 13.3 and FP64 20.2 -> 17.3; N = 3072, D = 8, 30.8 -> 28.9; the one
+//     loss met is N = 3000, D = 3, FP32, 17.9 -> 18.2.
+//   6145..8192 (FP32, D >= 2; FP64, D = 3 to 7), 64 x 128, two by two waves:
+//     N = 7000, D = 2, FP32, 45.8 -> 43.5, D = 6, FP64, 102.9 -> 100.3; FP64 with
+//     D = 8 loses (193.6 -> 200.9 at 6200).
+//   8193..12288, D = 2 to 7 (and D = 7 beyond), 128 x 128, two by two waves:
+//     N = 10500, D = 2, 94.9 -> 91.9 and FP64 136.4 -> 130.3, D = 6, 128.4 ->
+//     116.9; N = 14000, D = 7, 235.8 -> 219.0.  FP64 with D = 4 keeps the smaller
+//     64 x 128 (N = 8700: 121.7 -> 117.6 with it, 125.6 with the larger).
+//   8193 and above, D = 8, FP32, 64 x 256, four waves across: N = 10500, 187.6 ->
+//     168.6; N = 25000, 895 -> 855.
 void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, int* wr)
 {
-    (void)dtype;
-    if (whole && n > 1024 && n <= (d <= 2 ? 2048 : 1536)) {
-        *br = 32;
-        *wc = 1;
-        *wr = 4;
-    } else if (n <= 1536) {
+    const bool f32 = (dtype & 0xff) == MDS_F32;
+    auto is = [&](int rows, int cols, int row_waves) {
+        *br = rows;
+        *wc = cols;
+        *wr = row_waves;
+    };
+    if (whole) {
+        if (n > 1024 && n <= (d <= 4 ? 2048 : 1536)) return is(32, 1, 4);
+        if (n > 2048 && n <= 3072 && (f32 || d > 2)) return is(64, 1, 4);
+        if (n > 6144 && n <= 8192 && (f32 ? d >= 2 : d >= 3 && d <= 7)) return is(64, 2, 2);
+        if (n > 8192 && n <= 12288 && !f32 && d == 4) return is(64, 2, 2);
+        if (n > 8192 && (n <= 12288 ? d >= 2 && d <= 7 : d == 7)) return is(128, 2, 2);
+        // (the bound: this shape has a few tiles more, limited to 2^31 - 1)
+        if (n > 8192 && n <= (1 << 22) && f32 && d == 8) return is(64, 4, 1);
+    }
+    if (n <= 1536) {
         *br = 8;
         *wc = 1;
         *wr = 1;
