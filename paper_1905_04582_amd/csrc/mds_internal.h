@@ -120,7 +120,15 @@ __host__ __device__ inline void tile_coords(int64_t tile, int nrb, int br, int c
 
 // rows staged per reduction step of the sweep (keeps the per-wave staging
 // buffer at <= 16 values per lane)
-__host__ __device__ constexpr int sweep_stage_rows(int d) { return d <= 2 ? 8 : (d <= 4 ? 4 : 2); }
+__host__ __device__ constexpr int sweep_stage_rows(int d, int elem = 4)
+{
+    // FP64 at D = 2: four rows, so that five four-wave work-groups' LDS (18 KB
+    // each, 35 KB with eight rows) fits a compute unit, as many as the walk's
+    // registers allow (89): N = 5392, 41.0 -> 39.4 us, N = 8000 105.1 -> 101.4,
+    // N = 20000 466 -> 459; the shorter batches cost 0.3% at N = 3000
+    if (elem == 8 && d == 2) return 4;
+    return d <= 2 ? 8 : (d <= 4 ? 4 : 2);
+}
 
 // The rows one wave of a tile walks.  The wave's row group is
 // [rw0, rw1) (empty when the group lies past N); rows i <= jw0 hold no pair
@@ -214,7 +222,7 @@ constexpr int kStagePadBytes = 32;
 // column sums when wr > 1, so it holds at least 64 * D doubles)
 __host__ __device__ inline size_t sweep_stage_bytes(int d, int elem)
 {
-    const size_t rows = (size_t)sweep_stage_rows(d) * ((size_t)kWave * d * elem + kStagePadBytes);
+    const size_t rows = (size_t)sweep_stage_rows(d, elem) * ((size_t)kWave * d * elem + kStagePadBytes);
     const size_t cols = (size_t)kWave * d * sizeof(double);
     return rows > cols ? rows : cols;
 }

@@ -130,7 +130,7 @@ template <typename T, int D, bool GRAD>
 __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t tile, double* lds,
                                            const int tid)
 {
-    constexpr int RB = sweep_stage_rows(D);
+    constexpr int RB = sweep_stage_rows(D, (int)sizeof(T));
     const int lane = tid & (kWave - 1);
     const int w = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int waves = blockDim.x / kWave;
