@@ -14,11 +14,12 @@ Everything is computed here from the mathematics with mpmath (50 digits):
   product exp(-z^2) erfcx(z) is 0 whatever erfcx is.  A second, shorter FP64
   rational covers [2.1, 6.6] only (t = z sqrt 2 from 2.97 to 9.33); the kernels
   no longer use it, its table stays for the test that checks it.
-* The FP64 sweep's near pairs need q = 1 - Phi(t) = e R(t), e = exp(-t^2/2)
-  and R(t) = erfcx(t/sqrt 2)/2, to an absolute error only (q enters as 1 - q),
-  so R is fitted as P(t)/Q(t), Q(0) = 1, with weight e on [0, 9] (9 the sweep's
-  skip point): a far shorter rational than a relative fit.  Its exponential is 2^f on |f| <= 1/2, a polynomial with
-  constant term 1 (Chebyshev interpolation of (2^f - 1)/f).
+* The FP64 sweeps' near pairs and the held-out density need q = 1 - Phi(t) =
+  e R(t), e = exp(-t^2/2) and R(t) = erfcx(t/sqrt 2)/2, to a relative error
+  (sums of -ln Phi may consist of far pairs alone), on [0, 9] only (9 the
+  sweep's skip point): R is fitted as P(t)/Q(t), Q(0) = 1, in relative error.
+  Their exponential is 2^f on |f| <= 1/2, a polynomial with constant term 1
+  (Chebyshev interpolation of (2^f - 1)/f).
 * exp(r) on |r| <= ln(2)/2 by its Taylor polynomial (FP64), after the
   Cody-Waite reduction x = k ln 2 + r with ln 2 split into a head with 20
   trailing zero bits and a tail.
@@ -88,11 +89,11 @@ def near_ratio(t):
 
 
 def fit_near(m: int, n: int, tmax, npts: int = 240, iters: int = 22):
-    """R(t) ~ P(t)/Q(t), deg P = m, deg Q = n, Q(0) = 1, on [0, tmax] with
-    weight exp(-t^2/2), by the same iteration as fit_erfcx."""
+    """R(t) ~ P(t)/Q(t), deg P = m, deg Q = n, Q(0) = 1, on [0, tmax] in
+    relative error, by the same iteration as fit_erfcx."""
     ts = [tmax * (1 - mp.cos(mp.pi * (k + mp.mpf(1) / 2) / npts)) / 2 for k in range(npts)]
     ys = [near_ratio(t) for t in ts]
-    wt = [mp.exp(-t * t / 2) for t in ts]
+    wt = [1 / y for y in ys]
     w, qprev, best = [mp.mpf(1)] * npts, [mp.mpf(1)] * npts, None
     for _ in range(iters):
         A, b = mp.matrix(npts, m + 1 + n), mp.matrix(npts, 1)
@@ -123,7 +124,7 @@ def check_near(p, q, tmax, dt):
     r = (horner_np([float(v) for v in p], ts, dt).astype(np.longdouble) /
          horner_np([float(v) for v in q], ts, dt).astype(np.longdouble))
     ref = np.array([float(near_ratio(mp.mpf(float(t)))) for t in ts], dtype=np.longdouble)
-    return float(np.max(np.abs(r - ref) * np.exp(-ts.astype(np.longdouble) ** 2 / 2)))
+    return float(np.max(np.abs(r - ref) / ref))
 
 
 def exp2_slope(f):
@@ -231,10 +232,10 @@ def main():
 
     # the sweep's near pairs
     tnear = mp.mpf(9)
-    pn, qn = fit_near(6, 7, tnear)
+    pn, qn = fit_near(8, 9, tnear)
     en = check_near(pn, qn, tnear, np.float64)
-    lines.append(f"// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, {tnear}] (FP64); worst absolute error "
-                 f"of exp(-t^2/2) P/Q {en:.2e} with FP64 arithmetic")
+    lines.append(f"// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, {tnear}] (FP64); worst relative error "
+                 f"{en:.2e} with FP64 coefficients")
     lines.append(emit_array("kNearP64", pn, np.float64))
     lines.append(emit_array("kNearQ64", qn, np.float64))
     e2 = [mp.mpf(1)] + cheb_fit(exp2_slope, -mp.mpf(1) / 2, mp.mpf(1) / 2, 10)

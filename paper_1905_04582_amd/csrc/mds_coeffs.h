@@ -73,25 +73,29 @@ constexpr double kErfcxFarQ64[8] = {
     0x1.bc87206f17fe2p-4,
     0x1.893e076c0501fp-7};
 
-// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, 9.0] (FP64); worst absolute error of exp(-t^2/2) P/Q 1.09e-16 with FP64 arithmetic
-constexpr double kNearP64[7] = {
+// erfcx(t/sqrt 2)/2 ~ P(t)/Q(t) on [0, 9.0] (FP64); worst relative error 6.21e-16 with FP64 coefficients
+constexpr double kNearP64[9] = {
     0x1.0000000000000p-1,
-    0x1.0123d7ff1a05cp-1,
-    0x1.048a255fe3197p-2,
-    0x1.3b4dc0833b57dp-4,
-    0x1.da0a7807e229cp-7,
-    0x1.a0a7478e177a7p-10,
-    0x1.4f95c0a2fc844p-14};
+    0x1.540ee0c705426p-1,
+    0x1.c2582417095a7p-2,
+    0x1.7680023cd4bd4p-3,
+    0x1.a61e8d4a7e6b0p-5,
+    0x1.484d931b82bedp-7,
+    0x1.57e8088229545p-10,
+    0x1.bd41e1e8e3bb7p-14,
+    0x1.133233092929bp-18};
 
-constexpr double kNearQ64[8] = {
+constexpr double kNearQ64[10] = {
     0x1.0000000000000p+0,
-    0x1.cd66019dbbbb2p+0,
-    0x1.72699b494c041p+0,
-    0x1.58b150a3fc54ep-1,
-    0x1.936b2b80d61d0p-3,
-    0x1.2aadb60993e59p-5,
-    0x1.051bdcd2e141fp-8,
-    0x1.a495ec5711708p-13};
+    0x1.10288532d37adp+1,
+    0x1.09bca9dbbc296p+1,
+    0x1.399b93a17a613p+0,
+    0x1.ee8ac3bcbfb3dp-2,
+    0x1.0f3753b4199cfp-3,
+    0x1.9fd3aa0134ecfp-6,
+    0x1.b05eb4dc521f4p-9,
+    0x1.17061008b501fp-12,
+    0x1.58e83abf6f9e2p-17};
 
 // 2^f on |f| <= 1/2, degree 11; worst relative error 2.12e-16
 constexpr double kExp2C64[12] = {

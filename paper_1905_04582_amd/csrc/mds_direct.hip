@@ -84,7 +84,7 @@ __global__ void __launch_bounds__(kWave * kDirectWaves) direct_kernel(DirectArgs
     const NearConst64 nc = near_const(sig, inv_s);
     const double thr2 = a.truncated ? (kSkipT * sig) * (kSkipT * sig) : -1.0;
     const tab64_ptr ctab = tab64();
-    double sA = 0.0, sM = 0.0, sG = 1.0;
+    double sA = 0.0, sM = 0.0, sE = 0.0;
     int cnt = 0, near_steps = 0;
 
     for (; ca < n; ca += 2 * kStride) {
@@ -119,12 +119,12 @@ __global__ void __launch_bounds__(kWave * kDirectWaves) direct_kernel(DirectArgs
         }
         if (ta | tb) {
             const double dla = s2a * rsa, dlb = s2b * rsb;
-            double ga, gb, mla, mlb;
+            double ua, ub, mla, mlb;
             near_terms2_f64(s2a, s2b, dla, dlb, __builtin_amdgcn_inverse_ballot_w64(ta),
-                            __builtin_amdgcn_inverse_ballot_w64(tb), nc, ctab, ga, gb, mla, mlb);
+                            __builtin_amdgcn_inverse_ballot_w64(tb), nc, ctab, ua, ub, mla, mlb);
             if constexpr (SCAL) {
                 near_steps = 1;
-                sG *= ga * gb;
+                sE = extend_product(sE, ua, ub);
                 sM = fma(dla, mla, sM);
                 sM = fma(dlb, mlb, sM);
             }
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(kWave * kDirectWaves) direct_kernel(DirectArgs
         if ((lane & 15) < kDirectRows) part[w * kGroups + lane / 16][ii * D + d] = v;
     }
     if constexpr (SCAL) {
-        const double lnphi = near_steps ? -log_product(sG, ctab) : 0.0;
+        const double lnphi = near_steps ? -log1p_product(sE, ctab) : 0.0;
         const double r = wave_sum(fma(sA, 0.5 * inv_s2, lnphi));
         const double s = wave_sum((sA + sM) * (inv_s2 * inv_s));
         if (lane == 0) {

@@ -11,8 +11,8 @@
 // q -> 0.  The two divisions share one reciprocal of (4Q - a)(4Q - 2a).
 // Coefficients come from gen_coeffs.py (mds_coeffs.h).  Every lane runs the
 // same instructions whatever t is: no branches, no lane divergence.  The FP64
-// sweep and the held-out density use shorter forms with an absolute error
-// (further down): what they add ln Phi and phi/Phi to is of order one.
+// sweep and the held-out density use shorter forms of the same precision on
+// their range of t (further down).
 //
 // The general helpers at the end also cover t < 0 (never reached by the
 // sweeps, where delta >= 0 and sigma > 0) through the log-erfc form
@@ -179,13 +179,15 @@ __device__ __forceinline__ void trunc_terms_f64(double t, double& lnphi, double&
 
 // The sweep's truncation terms.  Its sums need sum ln Phi(t) and m =
 // phi(t)/Phi(t) of each near pair (t below the sweep's skip point), and the
-// first only as a sum: it is -ln of the product of the pairs' 1/Phi, so a pair
-// costs one multiplication instead of a logarithm.  With e = exp(-t^2/2) and
-// 1 - Phi = e P/Q (fitted to an absolute error of 2^-53),
-//     1/Phi = Q / (Q - e P),   sigma m = (sigma/sqrt(2 pi)) e (1/Phi),
-// from one reciprocal.  Against the relative form above (84 instructions a
-// pair, 71 in a far-range variant) this is 45, in one form for every near t,
-// with 26 coefficients instead of 44.
+// first only as a sum: it is -ln of the product G of the pairs' 1/Phi, so a
+// pair costs a multiplication instead of a logarithm.  With e = exp(-t^2/2),
+// 1 - Phi = e P/Q (fitted in relative error, as the form above) and x = e P,
+//     u = 1/Phi - 1 = x / (Q - x),   sigma m = (sigma/sqrt(2 pi)) e (1 + u),
+// from one reciprocal.  The product is carried as E = G - 1, E' = E + u + E u,
+// and closed by ln(1 + E), so that a sum of small terms keeps its relative
+// precision (at t = 8 a term is 6e-16, which a factor 1/Phi would round away).
+// Against the form above (84 instructions a pair) this is 52, in one form for
+// every near t, with 32 coefficients instead of 44.
 
 // what the near terms take from sigma, formed once per wave
 struct NearConst64 {
@@ -212,11 +214,11 @@ __device__ __forceinline__ double near_scale(double p, double shifted)
 }
 
 // Two pairs, sharing every coefficient load: s2 = delta^2, dl = delta; `na`,
-// `nb`: whether the pair is near (one that is not gets g = 1 to rounding and
-// m = 0).  g = 1/Phi(t), m = sigma phi(t)/Phi(t).
+// `nb`: whether the pair is near (one that is not gets u = m = 0).
+// u = 1/Phi(t) - 1, m = sigma phi(t)/Phi(t).
 __device__ __forceinline__ void near_terms2_f64(double s2a, double s2b, double dla, double dlb,
                                                 bool na, bool nb, const NearConst64& k,
-                                                tab64_ptr tb, double& ga, double& gb, double& ma,
+                                                tab64_ptr tb, double& ua, double& ub, double& ma,
                                                 double& mb)
 {
     constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
@@ -235,16 +237,25 @@ __device__ __forceinline__ void near_terms2_f64(double s2a, double s2b, double d
     horner2_tab<kNearQN - 1>(tb->near_q + 1, ta, tb2, Qa, Qb);
     Qa = fma(Qa, ta, 1.0);
     Qb = fma(Qb, tb2, 1.0);
-    const double da = fma(-ea, Pa, Qa), db = fma(-eb, Pb, Qb);
-    // Q/d: the hardware reciprocal r (relative error v below 2^-22), then the
+    const double xa = ea * Pa, xb = eb * Pb;
+    const double da = Qa - xa, db = Qb - xb;
+    // x/d: the hardware reciprocal r (relative error v below 2^-22), then the
     // quotient by 1 + v + v^2
     const double ra = __builtin_amdgcn_rcp(da), rb = __builtin_amdgcn_rcp(db);
     const double va = fma(-da, ra, 1.0), vb = fma(-db, rb, 1.0);
-    const double qa = Qa * ra, qb = Qb * rb;
-    ga = fma(qa, fma(va, va, va), qa);
-    gb = fma(qb, fma(vb, vb, vb), qb);
-    ma = (ea * k.kappa) * ga;
-    mb = (eb * k.kappa) * gb;
+    const double qa = xa * ra, qb = xb * rb;
+    ua = fma(qa, fma(va, va, va), qa);
+    ub = fma(qb, fma(vb, vb, vb), qb);
+    const double ka = ea * k.kappa, kb = eb * k.kappa;
+    ma = fma(ka, ua, ka);
+    mb = fma(kb, ub, kb);
+}
+
+// E = G - 1 of a product G = (1 + E) with two more factors 1 + u
+__device__ __forceinline__ double extend_product(double E, double ua, double ub)
+{
+    const double u = fma(ua, ub, ua + ub);
+    return fma(E, u, E + u);
 }
 
 // -ln Phi(t) of two pairs in the same terms, 0 for a pair with near = false:
@@ -294,21 +305,24 @@ __device__ __forceinline__ void exp2_neg_f64(double x1, double x2, tab64_ptr tb,
     e2 = near_scale(fma(p2, f2, 1.0), h2);
 }
 
-// ln g for a product g of up to 256 factors 1/Phi in [1, 2] (to rounding):
-// g = 2^n h, h in [1/2, 1), ln h = ln c + 2 atanh((h - c)/(h + c)) about
-// c = sqrt(1/2), |(h - c)/(h + c)| < 0.172
-__device__ __forceinline__ double log_product(double g, tab64_ptr tb)
+// ln(1 + E), E >= 0, for the product 1 + E of up to 256 factors 1/Phi in
+// [1, 2]: 1 + E = 2^n f, f in [sqrt(1/2), sqrt 2), ln f = 2 atanh((f - 1)/(f + 1)),
+// the quotient below 0.172; where n = 0, f - 1 is E itself
+__device__ __forceinline__ double log1p_product(double E, tab64_ptr tb)
 {
     constexpr double kLn2 = 0.693147180559945309417;
-    const int n = __builtin_amdgcn_frexp_exp(g);
+    const double g = 1.0 + E;
     const double h = __builtin_amdgcn_frexp_mant(g);
-    const double d = h + kInvSqrt2;
+    const bool low = h < kInvSqrt2;
+    const int n = __builtin_amdgcn_frexp_exp(g) - (low ? 1 : 0);
+    const double f = low ? 2.0 * h : h;
+    const double d = f + 1.0;
     const double r = __builtin_amdgcn_rcp(d);
     const double v = fma(-d, r, 1.0);
-    const double q = (h - kInvSqrt2) * r;
+    const double q = (n == 0 ? E : f - 1.0) * r;
     const double s = fma(q, fma(v, v, v), q);
     const double a = horner_tab<kAtanhN>(tb->atanh, s * s);
-    return fma(2.0 * s, a, ((double)n - 0.5) * kLn2);
+    return fma(2.0 * s, a, (double)n * kLn2);
 }
 
 // ---------------------------------------------------------------- FP32 --

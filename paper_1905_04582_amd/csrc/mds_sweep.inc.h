@@ -21,12 +21,12 @@
 //     square, which both the likelihood and dL/dsigma scale by a power of
 //     1/sigma once per wave, and its gradient coefficient (scaled by
 //     1/sigma^2 once per staging batch in FP32, once per walk in FP64);
-//   * in FP64 a near pair costs 45 vector instructions more (near_terms2_f64);
+//   * in FP64 a near pair costs 52 vector instructions more (near_terms2_f64);
 //     the sweep is bound by vector issue (86% busy at N = 20000, the clock
 //     held near 1.8 GHz by the FP64 load), so they are most of its time where
 //     few wavefronts skip.  N = 20000, D = 2, sigma = 0.5: 579 -> 484 us per
 //     evaluation with them; N = 5392, sigma = 0.3: 50.2 -> 45.4 us.  FP32 keeps
-//     its relative forms: their roundings set the result's last digits;
+//     its own forms: their roundings set the result's last digits;
 //   * the column sums of the wr waves of a column group, and the row sums of
 //     the wc waves of a row group, meet in LDS and are added in wave order;
 //     column, row and scalar partials of the tile go to the workspace, and
@@ -165,9 +165,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
     // and M = sum delta phi(t)/Phi(t) (FP64: times sigma); the tile's r and
     // dsigma sums follow from them (r = A / (2 sigma^2) + L, dsigma terms = A /
     // sigma^3 + M / sigma^2), so a pair past the skip point adds one product to
-    // them.  FP64 carries L as G, the product of the near pairs' 1/Phi (at most
-    // 2^256 over a walk's 256 rows); FP32 sums -ln Phi / 2.
-    double acc_A = 0.0, acc_G = 1.0, acc_M = 0.0, acc_L = 0.0;
+    // them.  FP64 carries L as E = G - 1, G the product of the near pairs' 1/Phi
+    // (at most 2^256 over a walk's 256 rows); FP32 sums -ln Phi / 2.
+    double acc_A = 0.0, acc_E = 0.0, acc_M = 0.0, acc_L = 0.0;
     int cnt = 0;
     // sigma is read-only for the launch: a scalar load
     const double sig = *(const_f64_ptr)a.sigma;
@@ -240,23 +240,23 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
 
         constexpr bool BATCH_SUMS = sizeof(T) < sizeof(double);
         T gjb[D];
-        T bA, bG, bM;
+        T bA, bE, bM;
         auto batch_reset = [&]() {
 #pragma unroll
             for (int d = 0; d < D; ++d) gjb[d] = T(0);
             bA = T(0);
-            bG = BATCH_SUMS ? T(0) : T(1);
+            bE = T(0);
             bM = T(0);
         };
-        // In FP32 the lane sums (bA, bG, bM, gjb) close into the FP64
+        // In FP32 the lane sums (bA, bE, bM, gjb) close into the FP64
         // accumulators at the end of each staging batch; in FP64 they are
         // those accumulators and run over the whole walk.
         auto close_sums = [&]() {
             acc_A += (double)bA;
             if constexpr (BATCH_SUMS)
-                acc_L += -2.0 * (double)bG;
+                acc_L += -2.0 * (double)bE;
             else
-                acc_G = bG;
+                acc_E = bE;
             acc_M += (double)bM;
 #pragma unroll
             for (int d = 0; d < D; ++d) gj[d] = fma((double)gjb[d], inv_s2, gj[d]);
@@ -354,12 +354,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
                 T wa = ra, wb = rb;
                 if (na | nb) {
                     const T dla = s2a * rsa, dlb = s2b * rsb;
-                    T ga, gb, mla, mlb;
+                    T ua, ub, mla, mlb;
                     near_terms2_f64(s2a, s2b, dla, dlb, __builtin_amdgcn_inverse_ballot_w64(na),
-                                    __builtin_amdgcn_inverse_ballot_w64(nb), nc, ctab, ga, gb,
+                                    __builtin_amdgcn_inverse_ballot_w64(nb), nc, ctab, ua, ub,
                                     mla, mlb);
                     near_steps = 1;
-                    bG *= ga * gb;
+                    bE = extend_product(bE, ua, ub);
                     bM = fma(dla, mla, bM);
                     bM = fma(dlb, mlb, bM);
                     wa += mla;
@@ -375,7 +375,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
                     T ha, hb, mla, mlb;
                     near_terms_f32(dla * inv_sT, oka, ha, mla);
                     near_terms_f32(dlb * inv_sT, okb, hb, mlb);
-                    bG += ha + hb;
+                    bE += ha + hb;
                     bM = fma(dla, mla, bM);
                     bM = fma(dlb, mlb, bM);
                     ca = fma(mla * sigT, rsa, ca);
@@ -477,7 +477,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
             if (q != 0) batch_flush(general_walk, ib - q);
         }
         if constexpr (!BATCH_SUMS) close_sums();
-        if (near_steps) acc_L = -log_product(acc_G, ctab);
+        if (near_steps) acc_L = -log1p_product(acc_E, ctab);
     }
 
     double acc_r = fma(acc_A, 0.5 * inv_s2, acc_L);
