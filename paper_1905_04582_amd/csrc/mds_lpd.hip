@@ -211,19 +211,22 @@ constexpr int kLpdDrawChunk = 64;  // draws whose constants a block holds at a t
 
 struct DrawConst {
     double inv_sigma;
-    double c2;  // -log2(e) / (2 sigma^2)
     double c0;  // -ln(sqrt(2 pi) sigma)
 };
 
 // sqrt(s2): s2 / sqrt(s2) and one correction by its own residual, which leaves
 // the final rounding (z = (y - delta)/sigma magnifies an error of delta); the
-// rare values out of its range (infinite, NaN) go through the library's
+// rare values out of its range (0, squares so small that the residual
+// underflows, infinite, NaN) go through the library's
 __device__ __forceinline__ double lpd_distance(double s2)
 {
-    const double rs = rsqrt_f64(fmax(s2, 2.2250738585072014e-308));
+    constexpr uint32_t kLow = (1023u - 900u) << 20, kHigh = (1023u + 1000u) << 20;
+    const double rs = rsqrt_f64(s2);
     double delta = s2 * rs;
     delta = fma(fma(-delta, delta, s2), 0.5 * rs, delta);
-    if (__builtin_amdgcn_ballot_w64(!(s2 < 1e300))) delta = s2 < 1e300 ? delta : sqrt(s2);
+    // 2^-900 <= s2 < 2^1000, from the word that holds sign and exponent
+    const bool ok = (uint32_t)__double2hiint(s2) - kLow < kHigh - kLow;
+    if (__builtin_amdgcn_ballot_w64(!ok)) delta = ok ? delta : sqrt(s2);
     return delta;
 }
 
@@ -261,7 +264,7 @@ __global__ void __launch_bounds__(kLpdThreads)
         if ((int)threadIdx.x < chunk) {
             const double sigma = sigmas[s0 + threadIdx.x];
             const double inv = 1.0 / sigma;
-            dc[threadIdx.x] = {inv, -0.5 * kLog2e * inv * inv, -kLnSqrt2Pi - log(sigma)};
+            dc[threadIdx.x] = {inv, -kLnSqrt2Pi - log(sigma)};
         }
         __syncthreads();
         for (int sc = 0; sc < chunk; ++sc) {
@@ -285,7 +288,7 @@ __global__ void __launch_bounds__(kLpdThreads)
                 const bool na = ta < 9.0, nb = tb2 < 9.0;
                 double l[2] = {0.0, 0.0};
                 if (__builtin_amdgcn_ballot_w64(na) | __builtin_amdgcn_ballot_w64(nb))
-                    neg_ln_phi2_f64(s2[u], s2[u + 1], ta, tb2, na, nb, c.c2, tb, l[0], l[1]);
+                    neg_ln_phi2_f64(ta, tb2, na, nb, tb, l[0], l[1]);
                 const double za = (yv[u] - da) * c.inv_sigma;
                 const double zb = (yv[u + 1] - db) * c.inv_sigma;
                 l[0] += fma(-0.5 * za, za, c.c0);

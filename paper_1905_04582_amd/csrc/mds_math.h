@@ -259,15 +259,16 @@ __device__ __forceinline__ double extend_product(double E, double ua, double ub)
 }
 
 // -ln Phi(t) of two pairs in the same terms, 0 for a pair with near = false:
-// q = e P/Q, -ln Phi = 2 atanh(s) with s = q/(2 - q) = e P/(2Q - e P); c2 =
-// -log2(e) / (2 sigma^2) over s2 = delta^2
-__device__ __forceinline__ void neg_ln_phi2_f64(double s2a, double s2b, double ta, double tb2,
-                                                bool na, bool nb, double c2, tab64_ptr tb,
-                                                double& la, double& lb)
+// q = e P/Q, -ln Phi = 2 atanh(s) with s = q/(2 - q) = e P/(2Q - e P).  The
+// exponent is taken from t itself: sigma may be as small as a double holds.
+__device__ __forceinline__ void neg_ln_phi2_f64(double ta, double tb2, bool na, bool nb,
+                                                tab64_ptr tb, double& la, double& lb)
 {
     constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52
-    const double ha = fma(s2a, c2, kMagic), hb = fma(s2b, c2, kMagic);
-    const double fa = fma(s2a, c2, -(ha - kMagic)), fb = fma(s2b, c2, -(hb - kMagic));
+    constexpr double kC2 = -0.5 * kLog2e;
+    const double t2a = ta * ta, t2b = tb2 * tb2;
+    const double ha = fma(t2a, kC2, kMagic), hb = fma(t2b, kC2, kMagic);
+    const double fa = fma(t2a, kC2, -(ha - kMagic)), fb = fma(t2b, kC2, -(hb - kMagic));
     double pa, pb;
     horner2_tab<kExp2N - 1>(tb->exp2 + 1, fa, fb, pa, pb);
     pa = fma(pa, fa, 1.0);
