@@ -257,6 +257,8 @@ def main():
     lines.append(f"constexpr double kLn2Head = {float(head).hex()};")
     lines.append(f"constexpr double kLn2Tail = {float(tail).hex()};")
     lines.append(f"constexpr double kLog2e = {float(1 / ln2).hex()};")
+    lines.append(f"constexpr double kLog2eTail = {float(1 / ln2 - mp.mpf(float(1 / ln2))).hex()};"
+                 "  // log2(e) - kLog2e")
     lines.append(f"// Taylor polynomial of exp(r), degree {degx}; worst relative error {ex_err:.2e}")
     lines.append(emit_array("kExpC64", taylor, np.float64))
 

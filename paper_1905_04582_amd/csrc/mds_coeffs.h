@@ -117,6 +117,7 @@ constexpr double kExp2C64[12] = {
 constexpr double kLn2Head = 0x1.62e42fef00000p-1;
 constexpr double kLn2Tail = 0x1.473de6af278edp-34;
 constexpr double kLog2e = 0x1.71547652b82fep+0;
+constexpr double kLog2eTail = 0x1.777d0ffda0d24p-56;  // log2(e) - kLog2e
 // Taylor polynomial of exp(r), degree 12; worst relative error 3.14e-16
 constexpr double kExpC64[13] = {
     0x1.0000000000000p+0,

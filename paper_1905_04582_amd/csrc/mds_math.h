@@ -293,13 +293,15 @@ __device__ __forceinline__ void neg_ln_phi2_f64(double ta, double tb2, bool na, 
     lb = 2.0 * sb * Ab;
 }
 
-// exp(x) for -700 <= x <= 0 (2^f and an exponent, as above), two at a time
+// exp(x) for -700 <= x <= 0 (2^f and an exponent, as above; f takes the tail of
+// log2(e) too, whose product with x grows to 9 units of the result), two at a time
 __device__ __forceinline__ void exp2_neg_f64(double x1, double x2, tab64_ptr tb, double& e1,
                                              double& e2)
 {
     constexpr double kMagic = 6755399441055744.0;
     const double h1 = fma(x1, kLog2e, kMagic), h2 = fma(x2, kLog2e, kMagic);
-    const double f1 = fma(x1, kLog2e, -(h1 - kMagic)), f2 = fma(x2, kLog2e, -(h2 - kMagic));
+    const double f1 = fma(x1, kLog2eTail, fma(x1, kLog2e, -(h1 - kMagic)));
+    const double f2 = fma(x2, kLog2eTail, fma(x2, kLog2e, -(h2 - kMagic)));
     double p1, p2;
     horner2_tab<kExp2N - 1>(tb->exp2 + 1, f1, f2, p1, p2);
     e1 = near_scale(fma(p1, f1, 1.0), h1);
