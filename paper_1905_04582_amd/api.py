@@ -187,6 +187,15 @@ def _stream(stream=None, *tensors):
     return stream.cuda_stream
 
 
+def _read_count(cnt, stream) -> int:
+    """A device count as a number, read on the stream that its kernel was
+    enqueued on (a read on another stream does not wait for the kernel)."""
+    if stream is None:
+        return int(cnt.item())
+    with torch.cuda.stream(stream):
+        return int(cnt.item())
+
+
 def _ycode(y, truncated: bool) -> int:
     return _dtype_code(y.dtype) | (0 if truncated else MDS_UNTRUNCATED)
 
@@ -323,10 +332,10 @@ def mds_check_symmetric(y: torch.Tensor, stream=None) -> int:
     synchronises to read the count."""
     _check_mat(y, "y", y.dtype)
     n = y.shape[0]
-    cnt = torch.zeros((), dtype=torch.int64, device=y.device)
+    cnt = torch.empty((), dtype=torch.int64, device=y.device)
     _check(lib().mds_check_symmetric(_ptr(y), _dtype_code(y.dtype), _ld(y), n, _ptr(cnt),
                                      _stream(stream, y, cnt)), "mds_check_symmetric")
-    return int(cnt.item())
+    return _read_count(cnt, stream)
 
 
 def mds_require_symmetric(y: torch.Tensor, stream=None):
@@ -856,7 +865,7 @@ class HeldOutPairs:
         _check(lib().mds_heldout_count(*args, _ptr(cnt), _ptr(ws), ws.numel(),
                                        _stream(stream, src, h, m, cnt, ws)),
                "mds_heldout_count")
-        self.m = int(cnt.item())
+        self.m = _read_count(cnt, stream)
         k = max(self.m, 1)
         self.pi = torch.empty(k, dtype=torch.int32, device=dev)
         self.pj = torch.empty(k, dtype=torch.int32, device=dev)
