@@ -335,12 +335,17 @@ FinalizeArgs finalize_args(const Tiling& t, const SweepArgs& s)
 
 // The small-problem form: FP64, the caller leaving the tiling to the library
 // (a caller that names one gets the tiled sweep, whose results a batch with
-// that tiling reproduces), at most kDirectMaxN locations, 32-bit element
-// offsets, and no per-wave trace asked for.
-// Beyond kDirectMaxN evaluating each pair twice costs more than the second
-// launch (D = 2, N = 1280: 11.2 us a step against 11.3, N = 1536: 13.2 against
-// 12.6; D = 6, N = 1536: 16.4 against 16.0).
-constexpr int64_t kDirectMaxN = 1280;
+// that tiling reproduces), few enough locations, 32-bit element offsets, and no
+// per-wave trace asked for.
+// The line is where the work-groups of four rows outnumber the 256 compute units:
+// past it some hold two and the launch takes almost twice as long.  A gradient
+// with L, direct against the tiled sweep's best default shape: D = 2, N = 1000,
+// 9.2 : 9.8 us, N = 1025, 11.9 : 9.8, N = 1280, 14.4 : 10.0 (Y read for the first
+// time, 15.9 : 11.3); D = 7, N = 1000, 11.1 : 10.9, N = 1200, 18.5 : 12.1.  Without
+// L: D = 2, N = 1000, 5.8 : 9.7, N = 1025, 8.3 : 9.8, N = 1100, 9.2 : 9.9.  With
+// D = 8 the sweep's registers leave it further behind: N = 1025, 13.9 : 18.0 with
+// L, N = 1280, 18.1 : 18.7.
+constexpr int64_t direct_max_n(int d) { return d < 8 ? 1024 : 1280; }
 
 // its scratch: a second position buffer (N x D doubles), then the parts of the
 // scalar sums (two doubles and a count per work-group)
@@ -357,7 +362,7 @@ bool use_direct(int64_t n, int d, int y_dtype, int64_t ldx, int64_t ldy, int til
                 int tile_waves, const WorkspaceLayout& lay)
 {
     return y_dtype == MDS_F64 && tile_rows == 0 && tile_waves == 0 && n >= 2 &&
-           n <= kDirectMaxN && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
+           n <= direct_max_n(d) && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
            direct_bytes(n, d) <= lay.total && !g_tile_trace;
 }
 

@@ -10,12 +10,11 @@
 // work-group, and the kick and drift of the row follow in the same launch.
 // The drifted positions go to another buffer than the ones the launch reads
 // (other work-groups still need them).  Pairs evaluated twice cost what the
-// tiled sweep's small tiles cost in prologues and row reductions.  Per step of a
-// captured trajectory, D = 2, against the best tiling of the sweep: N = 60, 4.4
-// and 8.7 us; N = 257, 4.9 and 9.5; N = 1000, 7.3 and 10.9; N = 1280, 11.2 and
-// 11.3; N = 1536, 13.2 and 12.6.  (Four rows: with two or eight, or 16 waves,
-// N = 1000 takes 7.6, 10.3 and 7.5; the segments below the diagonal and the
-// number of work-groups pull in opposite directions.)
+// tiled sweep's small tiles cost in prologues and row reductions.  One gradient
+// of a captured sequence, D = 2, against the best tiling of the sweep: N = 60, 2.8
+// and 7.5 us; N = 257, 3.3 and 8.1; N = 1000, 5.8 and 9.7; N = 1280, 10.4 and 10.0.
+// (Four rows: with two or eight, or 16 waves, N = 1000 takes longer; the segments
+// below the diagonal and the number of work-groups pull in opposite directions.)
 //
 // Lane l of a wave holds row i0 + l % 4 and column c0 + l / 4 of a block of 16
 // columns; y comes from the strict lower triangle on either side of the
