@@ -437,10 +437,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
         };
         // A wave below the diagonal, all of its columns inside the problem
         // (most are), needs no mask but y's: two compares and two scalar ands
-        // fewer per step.  FP32: N = 5392, D = 6, 47.4 -> 44.6 us; N = 30011,
-        // D = 4, 727 -> 722 us.  FP64 with D <= 2 gains nothing (43.2 : 43.4
-        // us at N = 5392) and keeps one walk.
-        constexpr bool SPLIT = sizeof(T) == 4 || D > 2;
+        // fewer per step.  FP32: N = 5392, D = 6, 47.6 -> 44.6 us; N = 14000,
+        // D = 3, 177 -> 175, D = 6, 227 -> 206.  Where the second walk gains
+        // nothing there is one: FP64 with D <= 2 (43.2 : 43.4 us at N = 5392), and
+        // FP32 with D = 5 and 7, which it slows down (N = 700, D = 5, 9.7 -> 9.9;
+        // N = 14000, D = 5, 217.5 -> 221.2, D = 7, 222 -> 227).
+        constexpr bool SPLIT = sizeof(T) == 4 ? D != 5 && D != 7 : D > 2;
         if (SPLIT && fast && colmask == ~0ull && ib0 >= (int)wv.jw0 + kWave) {
             if constexpr (SPLIT) walk(full_walk);
         } else if (fast) {
