@@ -113,16 +113,25 @@ constexpr size_t kMaxSweepLds = 64 * 1024;
 //   1025..2048 (D <= 4; 1536 above), 32 rows over four waves: their 8-row tiles
 //     of one wave outnumber the chip's 1024 SIMDs.  FP32, N = 1280, D = 2 and 6,
 //     10.7 -> 8.5 and 13.9 -> 10.4 us; FP64, N = 1600, D = 3, 14.0 -> 12.3;
-//     above the line D = 6, FP64, loses (20.3 -> 21.2 us a leapfrog step).
+//     above the line D = 6, FP64, loses (20.3 -> 21.2 us a leapfrog step).  The
+//     log-likelihood alone gains or stays (N = 1300, FP64, D = 2, 9.4 -> 8.3 us),
+//     but for FP32 with D = 8 (N = 1025, 7.0 -> 7.3, the gradient 12.8 -> 11.8).
 //   2049..3072 (FP32, or D > 2), 64 rows over four waves: N = 2300, D = 3,
-//     14.6 -> 13.3 and FP64 20.2 -> 17.3; N = 3072, D = 8, 30.8 -> 28.9; the one
-//     loss met is N = 3000, D = 3, FP32, 17.9 -> 18.2.
+//     14.6 -> 13.3 and FP64 20.2 -> 17.3; N = 3072, D = 8, 30.8 -> 28.9.  (The
+//     log-likelihood alone, FP32 in spatial order at 2049, 9.2 -> 9.7 with D = 3.)
 //   6145..8192 (FP32, D >= 2; FP64, D = 3 to 7), 64 x 128, two by two waves:
 //     N = 7000, D = 2, FP32, 45.8 -> 43.5, D = 6, FP64, 102.9 -> 100.3; FP64 with
 //     D = 8 loses (193.6 -> 200.9 at 6200).
+//     FP32 goes on to 9216 (10240 with D = 2 and 3): 128 x 128 there loses in the
+//     log-likelihood alone and, in spatial order, with D = 2 and 3 in the
+//     gradient too (earlier shape : this one : 128 x 128; N = 8320, D = 3, ordered,
+//     55.8 : 53.7 : 57.0 and alone 39.1 : 38.1 : 42.3; N = 9088, D = 7, 108.6 : 105.1 :
+//     101.1 and 51.7 : 49.9 : 53.2).  D = 4 differs by 1% (66.2 : 65.2 at 8193).
 //   8193..12288, D = 2 to 7 (and D = 7 beyond), 128 x 128, two by two waves:
 //     N = 10500, D = 2, 94.9 -> 91.9 and FP64 136.4 -> 130.3, D = 6, 128.4 ->
-//     116.9; N = 14000, D = 7, 235.8 -> 219.0.  FP64 with D = 4 keeps the smaller
+//     116.9; N = 14000, D = 7, 235.8 -> 219.0.  (The log-likelihood alone, FP32
+//     with D = 6 and 7, loses up to 4%: N = 12288, D = 6, 80.1 -> 83.5, beside a
+//     gradient of 187 -> 156.)  FP64 with D = 4 keeps the smaller
 //     64 x 128 (N = 8700: 121.7 -> 117.6 with it, 125.6 with the larger).
 //   8193 and above, D = 8, FP32, 64 x 256, four waves across: N = 10500, 187.6 ->
 //     168.6; N = 25000, 895 -> 855.
@@ -138,6 +147,8 @@ void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, i
         if (n > 1024 && n <= (d <= 4 ? 2048 : 1536)) return is(32, 1, 4);
         if (n > 2048 && n <= 3072 && (f32 || d > 2)) return is(64, 1, 4);
         if (n > 6144 && n <= 8192 && (f32 ? d >= 2 : d >= 3 && d <= 7)) return is(64, 2, 2);
+        if (n > 8192 && n <= (d <= 3 ? 10240 : 9216) && f32 && d >= 2 && d <= 7 && d != 4)
+            return is(64, 2, 2);
         if (n > 8192 && n <= 12288 && !f32 && d == 4) return is(64, 2, 2);
         if (n > 8192 && (n <= 12288 ? d >= 2 && d <= 7 : d == 7)) return is(128, 2, 2);
         // (the bound: this shape has a few tiles more, limited to 2^31 - 1)

@@ -1,0 +1,18 @@
+"""Lines of the default tile rule that follow from both the gradient and the
+log-likelihood alone, and from the size of the workspace."""
+import pytest
+
+from paper_1905_04582_amd import api
+
+F64, F32 = api.MDS_F64, api.MDS_F32
+tw = api.tile_waves
+
+
+@pytest.mark.parametrize("n,d,dtype,shape", [
+    (8193, 2, F32, (64, tw(2, 2))), (10240, 3, F32, (64, tw(2, 2))),
+    (10241, 3, F32, (128, tw(2, 2))), (8193, 5, F32, (64, tw(2, 2))),
+    (9216, 7, F32, (64, tw(2, 2))), (9217, 7, F32, (128, tw(2, 2))),
+    (8193, 6, F64, (128, tw(2, 2))), (9216, 1, F32, (64, tw(1, 2))),
+])
+def test_shape_lines(n, d, dtype, shape):
+    assert api.mds_resolve_tiling(n, d, dtype) == shape
