@@ -133,8 +133,10 @@ constexpr size_t kMaxSweepLds = 64 * 1024;
 //     with D = 6 and 7, loses up to 4%: N = 12288, D = 6, 80.1 -> 83.5, beside a
 //     gradient of 187 -> 156.)  FP64 with D = 4 keeps the smaller
 //     64 x 128 (N = 8700: 121.7 -> 117.6 with it, 125.6 with the larger).
-//   8193 and above, D = 8, FP32, 64 x 256, four waves across: N = 10500, 187.6 ->
-//     168.6; N = 25000, 895 -> 855.
+//   8193..32768, D = 8, FP32, 64 x 256, four waves across: N = 10500, 187.6 ->
+//     168.6; N = 25000, 895 -> 855.  Its partial sums take 1.5 times the memory of
+//     the 128 x 128 before it (N = 32768: 1.21 GB for 0.81), so it ends where that
+//     begins to weigh beside Y (N = 240000: 65 GB for 43, with 230 of Y).
 void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, int* wr)
 {
     const bool f32 = (dtype & 0xff) == MDS_F32;
@@ -151,8 +153,7 @@ void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, i
             return is(64, 2, 2);
         if (n > 8192 && n <= 12288 && !f32 && d == 4) return is(64, 2, 2);
         if (n > 8192 && (n <= 12288 ? d >= 2 && d <= 7 : d == 7)) return is(128, 2, 2);
-        // (the bound: this shape has a few tiles more, limited to 2^31 - 1)
-        if (n > 8192 && n <= (1 << 22) && f32 && d == 8) return is(64, 4, 1);
+        if (n > 8192 && n <= 32768 && f32 && d == 8) return is(64, 4, 1);
     }
     if (n <= 1536) {
         *br = 8;

@@ -16,3 +16,15 @@ tw = api.tile_waves
 ])
 def test_shape_lines(n, d, dtype, shape):
     assert api.mds_resolve_tiling(n, d, dtype) == shape
+
+
+@pytest.mark.parametrize("n,d,dtype", [(32769, 8, F32), (60000, 8, F32), (240000, 8, F32),
+                                       (60000, 8, F64), (60000, 2, F32)])
+def test_workspace_of_large_problems(n, d, dtype):
+    # no more partial sums than tiles of 128 x 128 leave
+    assert api.mds_workspace_bytes(n, d, dtype) <= api.mds_workspace_bytes(n, d, dtype, 128, 2)
+
+
+def test_shape_before_the_workspace_weighs():
+    assert api.mds_resolve_tiling(32768, 8, F32) == (64, 4)
+    assert api.mds_resolve_tiling(32769, 8, F32) == (128, 2)
