@@ -379,14 +379,19 @@ bool use_direct(int64_t n, int d, int y_dtype, int64_t ldx, int64_t ldy, int til
 }
 
 // whether an output of n rows of d doubles may share memory with n rows of an
-// input (by the extent of both): the small-problem form reads every location and
-// its part of Y while it writes gradient rows
+// input: the small-problem form reads every location and its part of Y while it
+// writes gradient rows.  Rows side by side in one array (equal strides) share
+// nothing; otherwise overlapping extents count.
 bool rows_overlap(const double* out, int64_t ldo, int d, const void* in, int64_t ldi_bytes,
                   int64_t row_bytes, int64_t n)
 {
     const uintptr_t o0 = (uintptr_t)out, o1 = o0 + (uintptr_t)(((n - 1) * ldo + d) * 8);
     const uintptr_t i0 = (uintptr_t)in, i1 = i0 + (uintptr_t)((n - 1) * ldi_bytes + row_bytes);
-    return o0 < i1 && i0 < o1;
+    if (o0 >= i1 || i0 >= o1) return false;
+    if (ldo * 8 != ldi_bytes) return true;
+    // the output row's place within the input's stride
+    const int64_t at = (((int64_t)(o0 - i0)) % ldi_bytes + ldi_bytes) % ldi_bytes;
+    return at < row_bytes || at + (int64_t)d * 8 > ldi_bytes;
 }
 
 // the arguments every launch of it shares
