@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(kWave * kDirectWaves) direct_kernel(DirectArgs
     if constexpr (SCAL) {
         const double lnphi = near_steps ? -log1p_product(sE, ctab) : 0.0;
         const double r = wave_sum(fma(sA, 0.5 * inv_s2, lnphi));
-        const double s = wave_sum((sA + sM) * (inv_s2 * inv_s));
+        const double s = wave_sum(((sA + sM) * inv_s2) * inv_s);
         if (lane == 0) {
             scal[0][w] = 0.5 * r;
             scal[1][w] = 0.5 * s;

@@ -483,7 +483,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs& a, const int64_t til
     }
 
     double acc_r = fma(acc_A, 0.5 * inv_s2, acc_L);
-    double acc_s = sizeof(T) == 8 ? (acc_A + acc_M) * (inv_s2 * inv_s)
+    // (FP64: by 1/sigma^2 and then 1/sigma, whose product leaves the range of a
+    // double long before the sums do)
+    double acc_s = sizeof(T) == 8 ? ((acc_A + acc_M) * inv_s2) * inv_s
                                   : fma(acc_A, inv_s2 * inv_s, acc_M * inv_s2);
 
     const int wr = a.wr;
