@@ -205,7 +205,19 @@ __global__ void __launch_bounds__(kRowThreads)
 // locations, 0.39 M pairs, ten draws: 38.8 -> 32.0 us against blocks of 256
 // threads with four pairs) and large ones end evenly (1.45 M pairs: 86.6 -> 85.3
 // us; six dimensions, twelve draws, 2.9 M pairs: 215 -> 200 us).
-constexpr int kLpdThreads = kWave;
+// One draw per pass: blocks of four waves start sooner (0.39 M pairs, D = 2: 6.6 ->
+// 6.1 us, D = 6: 7.3 -> 6.8; 1.45 M, D = 2: 13.9 -> 13.5), except for lists that
+// leave the chip empty (12 000 pairs: 4.6 us, 4.8 with four waves) and, from D = 5
+// on, long ones, which one-wave blocks end sooner (1.45 M pairs, D = 6: 16.7 with
+// four, 15.6).  From D = 5 on each thread forms the constants itself, without a
+// barrier (D = 6, 0.39 M pairs: 6.84 -> 6.79).
+constexpr int kLpdThreads = kWave;           // several draws
+constexpr int kLpdOneThreads = 4 * kWave;    // one draw, at most
+inline int lpd_threads(bool one, int d, int64_t m)
+{
+    const bool four = m >= (1 << 17) && (d <= 4 || m < (1 << 20));
+    return one && four ? kLpdOneThreads : kLpdThreads;
+}
 constexpr int kLpdPairs = 2;
 constexpr int kLpdDrawChunk = 64;  // draws whose constants a block holds at a time
 
@@ -231,15 +243,17 @@ __device__ __forceinline__ double lpd_distance(double s2)
 }
 
 template <int D, bool ONE>
-__global__ void __launch_bounds__(kLpdThreads)
+__global__ void __launch_bounds__(ONE ? kLpdOneThreads : kLpdThreads)
     lpd_accumulate_kernel(int64_t m, const int32_t* __restrict__ pi, const int32_t* __restrict__ pj,
                           const double* __restrict__ py, const double* __restrict__ xs,
                           int64_t ldx, int64_t xstride, const double* __restrict__ sigmas,
                           int32_t n_draws, double* __restrict__ acc, int first)
 {
     constexpr double kLnSqrt2Pi = 0.91893853320467274178;
-    constexpr int T = kLpdThreads, P = kLpdPairs;
-    static_assert(P % 2 == 0 && T >= kLpdDrawChunk, "pairs and threads");
+    constexpr int P = kLpdPairs;
+    static_assert(P % 2 == 0 && kLpdThreads >= kLpdDrawChunk, "pairs and threads");
+    const int T = ONE ? (int)blockDim.x : kLpdThreads;
+    constexpr bool OWN = ONE && D > 4;
     __shared__ DrawConst dc[ONE ? 1 : kLpdDrawChunk];
     const int64_t base = (int64_t)blockIdx.x * (T * P) + threadIdx.x;
     int64_t ii[P], jj[P];
@@ -260,15 +274,17 @@ __global__ void __launch_bounds__(kLpdThreads)
     const tab64_ptr tb = tab64();
     for (int s0 = 0; s0 < draws; s0 += kLpdDrawChunk) {
         const int chunk = ONE ? 1 : min(draws - s0, kLpdDrawChunk);
-        __syncthreads();
-        if ((int)threadIdx.x < chunk) {
-            const double sigma = sigmas[s0 + threadIdx.x];
-            const double inv = 1.0 / sigma;
-            dc[threadIdx.x] = {inv, -kLnSqrt2Pi - log(sigma)};
+        auto constants = [&](int k) {
+            const double sigma = sigmas[s0 + k];
+            return DrawConst{1.0 / sigma, -kLnSqrt2Pi - log(sigma)};
+        };
+        if constexpr (!OWN) {
+            __syncthreads();
+            if ((int)threadIdx.x < chunk) dc[threadIdx.x] = constants(threadIdx.x);
+            __syncthreads();
         }
-        __syncthreads();
         for (int sc = 0; sc < chunk; ++sc) {
-            const DrawConst c = dc[sc];
+            const DrawConst c = OWN ? constants(0) : dc[sc];
             const double* x = xs + (int64_t)(s0 + sc) * xstride;
             const bool start = first && s0 + sc == 0;
             double s2[P];
@@ -422,8 +438,9 @@ hipError_t launch_lpd_accumulate(int64_t m, const int32_t* pi, const int32_t* pj
                                  double* acc, int first, hipStream_t s)
 {
     if (m == 0 || n_draws == 0) return hipSuccess;
-    const int64_t per_block = kLpdThreads * kLpdPairs;
-    const dim3 grid((unsigned)((m + per_block - 1) / per_block)), block(kLpdThreads);
+    const int threads = lpd_threads(n_draws == 1, d, m);
+    const int64_t per_block = threads * kLpdPairs;
+    const dim3 grid((unsigned)((m + per_block - 1) / per_block)), block(threads);
 #define MDS_LPD_CASE(DD)                                                                     \
     case DD:                                                                                 \
         if (n_draws == 1)                                                                    \
