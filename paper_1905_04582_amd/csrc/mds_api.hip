@@ -350,14 +350,18 @@ FinalizeArgs finalize_args(const Tiling& t, const SweepArgs& s)
 // that tiling reproduces), few enough locations, 32-bit element offsets, and no
 // per-wave trace asked for.
 // The line is where the work-groups of four rows outnumber the 256 compute units:
-// past it some hold two and the launch takes almost twice as long.  A gradient
-// with L, direct against the tiled sweep's best default shape: D = 2, N = 1000,
-// 9.2 : 9.8 us, N = 1025, 11.9 : 9.8, N = 1280, 14.4 : 10.0 (Y read for the first
-// time, 15.9 : 11.3); D = 7, N = 1000, 11.1 : 10.9, N = 1200, 18.5 : 12.1.  Without
-// L: D = 2, N = 1000, 5.8 : 9.7, N = 1025, 8.3 : 9.8, N = 1100, 9.2 : 9.9.  With
-// D = 8 the sweep's registers leave it further behind: N = 1025, 13.9 : 18.0 with
-// L, N = 1280, 18.1 : 18.7.
-constexpr int64_t direct_max_n(int d) { return d < 8 ? 1024 : 1280; }
+// past it some hold two and the launch takes longer by half and then twice as
+// long.  A gradient with L, direct against the tiled sweep's best default shape:
+// D = 2, N = 1000, 9.2 : 9.8 us, N = 1025, 11.9 : 9.8, N = 1280, 14.4 : 10.0 (Y read
+// for the first time, 15.9 : 11.3); D = 7, N = 1000, 11.1 : 10.9, N = 1200, 18.5 :
+// 12.1.  A trajectory needs L at its end alone and goes on to 1100 with D <= 6:
+// per step D = 1, N = 1025, 7.9 : 9.3, N = 1100, 9.0 : 9.5, N = 1200, 9.6 : 9.5; D = 6,
+// N = 1100, 11.2 : 11.9; D = 7, N = 1100, 13.3 : 11.9.  With D = 8 the sweep's registers
+// leave it further behind: N = 1025, 13.9 : 18.0 with L, N = 1280, 18.1 : 18.7.
+constexpr int64_t direct_max_n(int d, bool trajectory)
+{
+    return d >= 8 ? 1280 : (trajectory && d <= 6 ? 1100 : 1024);
+}
 
 // its scratch: a second position buffer (N x D doubles), then the parts of the
 // scalar sums (two doubles and a count per work-group)
@@ -371,10 +375,10 @@ size_t direct_bytes(int64_t n, int d)
 // (the scratch fits what the tiled sweep's partial sums would take, at least 24 N
 // D bytes; one location has no pair and may come without a Y)
 bool use_direct(int64_t n, int d, int y_dtype, int64_t ldx, int64_t ldy, int tile_rows,
-                int tile_waves, const WorkspaceLayout& lay)
+                int tile_waves, const WorkspaceLayout& lay, bool trajectory = false)
 {
     return y_dtype == MDS_F64 && tile_rows == 0 && tile_waves == 0 && n >= 2 &&
-           n <= direct_max_n(d) && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
+           n <= direct_max_n(d, trajectory) && ldy < ((int64_t)1 << 28) / n && ldx < ((int64_t)1 << 28) / n &&
            direct_bytes(n, d) <= lay.total && !g_tile_trace;
 }
 
@@ -778,7 +782,7 @@ int mds_leapfrog(int64_t n, int32_t d, double* x, int64_t ldx, double* p, int64_
 
     // grad log pi and L at a point: sweep + finalize, optionally followed by
     // a kick of mult*eps and a drift of eps, fused into the finalize
-    const bool direct = use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay);
+    const bool direct = use_direct(n, d, y_dtype, ldx, ldy, tile_rows, tile_waves, lay, true);
     double* xbuf = nullptr;  // direct: the positions alternate between x and this buffer
     DirectArgs da = direct_args(workspace, n, d, x, ldx, y, ldy, sigma_dev, trunc, &xbuf);
     da.prior = prior_dev;
