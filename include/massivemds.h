@@ -57,9 +57,12 @@
  *     plain count (wr = 0 in the second byte) means wr = 1.  One of
  *     tile_rows and 64*wc must divide the other.  The workspace depends on
  *     tile_rows and wc only, and must be sized with the same values.  With
- *     both 0, small FP64 problems (about a thousand locations) are evaluated
- *     without tiles, whole gradient rows at a time: the same sums in another
- *     order, so their last digits differ from those of a named tiling.
+ *     both 0, mds_gradient of a small FP64 problem (up to 1024 locations, 1280
+ *     with D = 8) whose gradient shares no memory with X or Y, and
+ *     trajectories (up to 1100 with D <= 6), are evaluated without tiles,
+ *     whole gradient rows at a time: the same sums in another order, so their
+ *     last digits differ from those of a named tiling, and L of mds_gradient
+ *     there from that of mds_loglik, which is always tiled.
  */
 #ifndef MASSIVEMDS_H
 #define MASSIVEMDS_H
@@ -126,7 +129,8 @@ MDS_API int mds_workspace_bytes(int64_t n, int32_t d, int32_t y_dtype, int32_t t
 /*
  * The tiling the sweeps use for these arguments: tile_rows / tile_waves as
  * passed to mds_loglik and friends (0 = the library's default for n, d and
- * y_dtype), resolved and validated.  Writes *rows_out (rows per tile) and
+ * y_dtype), resolved and validated; it sizes the workspace also where a small
+ * FP64 problem with both 0 is evaluated without tiles (above).  Writes *rows_out (rows per tile) and
  * *waves_out (the resolved MDS_TILE_WAVES(wc, wr); a plain count wc when
  * wr = 1);
  * returns a status (an unsupported tiling is MDS_ERR_UNSUPPORTED, as in the

@@ -124,7 +124,7 @@ __host__ __device__ constexpr int sweep_stage_rows(int d, int elem = 4)
 {
     // FP64 at D = 2: four rows, so that five four-wave work-groups' LDS (18 KB
     // each, 35 KB with eight rows) fits a compute unit, as many as the walk's
-    // registers allow (89): N = 5392, 41.0 -> 39.4 us, N = 8000 105.1 -> 101.4,
+    // registers allow (90): N = 5392, 41.0 -> 39.4 us, N = 8000 105.1 -> 101.4,
     // N = 20000 466 -> 459; the shorter batches cost 0.3% at N = 3000
     if (elem == 8 && d == 2) return 4;
     return d <= 2 ? 8 : (d <= 4 ? 4 : 2);

@@ -194,11 +194,11 @@ __global__ void __launch_bounds__(kRowThreads)
 // does not depend on how the draws are grouped into calls: S calls of one draw
 // and one call of S draws give the same bits.
 //
-// Several draws per pass are bound by vector instructions (129 per pair
+// Several draws per pass are bound by vector instructions (135 per pair
 // and draw with the short forms of mds_math.h; the library's exp, log and sqrt
-// and a relative ln Phi took 190), one draw per pass by the pair list and the
-// state it streams.  1.45 M pairs, D = 2, ten draws and the finalize: 102 -> 85
-// us (73% of the issue slots busy).
+// and the full-range ln Phi took 190), one draw per pass by the pair list and
+// the state it streams.  1.45 M pairs, D = 2, ten draws and the finalize: 100 ->
+// 86 us.
 //
 // Two pairs per thread (the special functions take two at a time) and blocks of
 // one wave: the most work-groups, so that small lists fill the chip (2800

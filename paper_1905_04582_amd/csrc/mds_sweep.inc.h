@@ -24,9 +24,10 @@
 //   * in FP64 a near pair costs 52 vector instructions more (near_terms2_f64);
 //     the sweep is bound by vector issue (86% busy at N = 20000, the clock
 //     held near 1.8 GHz by the FP64 load), so they are most of its time where
-//     few wavefronts skip.  N = 20000, D = 2, sigma = 0.5: 579 -> 484 us per
-//     evaluation with them; N = 5392, sigma = 0.3: 50.2 -> 45.4 us.  FP32 keeps
-//     its own forms: their roundings set the result's last digits;
+//     few wavefronts skip.  N = 20000, D = 2, sigma = 0.5: 560 us per evaluation
+//     with the full- and far-range forms (84 and 71 instructions), 478 with these
+//     and the shorter distances below; N = 5392, sigma = 0.3: 47.2 and 41.1 us.
+//     FP32 keeps its own forms: their roundings set the result's last digits;
 //   * the column sums of the wr waves of a column group, and the row sums of
 //     the wc waves of a row group, meet in LDS and are added in wave order;
 //     column, row and scalar partials of the tile go to the workspace, and
