@@ -94,6 +94,8 @@ int split_ytype(int32_t& y_dtype, int* truncated)
 
 // Largest LDS a sweep work-group may use (row sums of all its waves).
 constexpr size_t kMaxSweepLds = 64 * 1024;
+// the partial sums that mds_gradient_noalloc holds
+constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 
 // Tile shape used when the caller passes 0: the autotuner's grid on
 // spatially ordered random problems (D = 2, 4, 6; both precisions) rounded
@@ -127,6 +129,8 @@ constexpr size_t kMaxSweepLds = 64 * 1024;
 //     gradient too (earlier shape : this one : 128 x 128; N = 8320, D = 3, ordered,
 //     55.8 : 53.7 : 57.0 and alone 39.1 : 38.1 : 42.3; N = 9088, D = 7, 108.6 : 105.1 :
 //     101.1 and 51.7 : 49.9 : 53.2).  D = 4 differs by 1% (66.2 : 65.2 at 8193).
+//     Where only 128 x 128 leaves few enough partial sums for
+//     mds_gradient_noalloc (D = 3 from 8385, D = 5 to 8320), it stays.
 //   8193..12288, D = 2 to 7 (and D = 7 beyond), 128 x 128, two by two waves:
 //     N = 10500, D = 2, 94.9 -> 91.9 and FP64 136.4 -> 130.3, D = 6, 128.4 ->
 //     116.9; N = 14000, D = 7, 235.8 -> 219.0.  (The log-likelihood alone, FP32
@@ -145,11 +149,17 @@ void default_tiling(int64_t n, int d, int dtype, bool whole, int* br, int* wc, i
         *wc = cols;
         *wr = row_waves;
     };
+    // whether the partial sums of tiles 128 columns wide fit the static scratch
+    auto fits_scratch = [&](int rows) {
+        return workspace_layout(make_tiling(n, rows, 2, 2, f32 ? 4 : 8), d).total <=
+               kStaticScratchBytes;
+    };
     if (whole) {
         if (n > 1024 && n <= (d <= 4 ? 2048 : 1536)) return is(32, 1, 4);
         if (n > 2048 && n <= 3072 && (f32 || d > 2)) return is(64, 1, 4);
         if (n > 6144 && n <= 8192 && (f32 ? d >= 2 : d >= 3 && d <= 7)) return is(64, 2, 2);
-        if (n > 8192 && n <= (d <= 3 ? 10240 : 9216) && f32 && d >= 2 && d <= 7 && d != 4)
+        if (n > 8192 && n <= (d <= 3 ? 10240 : 9216) && f32 && d >= 2 && d <= 7 && d != 4 &&
+            (fits_scratch(64) || !fits_scratch(128)))
             return is(64, 2, 2);
         if (n > 8192 && n <= 12288 && !f32 && d == 4) return is(64, 2, 2);
         if (n > 8192 && (n <= 12288 ? d >= 2 && d <= 7 : d == 7)) return is(128, 2, 2);
@@ -442,7 +452,6 @@ hipError_t run_direct(int d, const DirectArgs& a, double* loglik, double* dsigma
 // static device array (each device holds its own copy for the life of the
 // process).  Host code never uses the array's name as an address: its device
 // address comes from hipGetSymbolAddress, once per device.
-constexpr size_t kStaticScratchBytes = size_t(32) << 20;
 constexpr int kMaxDevices = 64;
 __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
